@@ -10,6 +10,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <string>
@@ -41,8 +42,12 @@ template <typename T>
 struct Bufs {
   const T* X[4];
   const T* Z;
+  int ldx;      // row length of X and Z
+  int Kr;       // R_thc up to a whole 16-byte chunk (the products' K)
   T* W[4];
   T* Y;
+  T* HP;        // W_a o W_b, the right operand of the next core product
+  T* BP;        // W_p o Y, the right operand of the next back-projection
   T* Msol;
   T* Msave;
   T* Mbak;      // right-hand side kept for a damped retry of a fused solve
@@ -83,7 +88,7 @@ struct GroupOp {
   int total = 0;
   int count = 0;         // table entries
   int bm = 64;
-  bool a_t = false, b_t = false, had = false, apair = false, bpair = false;
+  bool a_t = false, b_t = false, apair = false, bpair = false;
   bool wide = false;     // split BF16: bm x 256 tiles (gemm_split_wide_group)
   int kparts = 1;        // split BF16, wide tiles: K slices (split-K) summed by a reduce launch
   int maxm = 0, maxn = 0;
@@ -147,8 +152,12 @@ struct cpd_plan_s {
   char* ws = nullptr;
   size_t ws_bytes = 0;
   size_t tables_off = 0;
+  size_t part_off = 0, part_bytes = 0;          // partial tiles of the split products
+  size_t cnt_off = 0;                           // their counters
+  int cnt_count = 0;
   int maxR = 0, maxTp = 0, maxNblk = 0, maxN = 0;
   GroupOp core[4], back[4], gram[4], proj[4];  // FP64 / FP32 MTTKRP, Gram, projection
+  GroupOp gramproj[4];                         // Gram and projection of a mode in one launch
   GroupOp score[4], sback[4], sproj[4];         // split-BF16 core / back / projection
   void* ftt[4] = {nullptr, nullptr, nullptr, nullptr};  // SplitTArgs per mode
   GroupOp fproj[3], fcore, fback;               // mixed: FP64 mode-3 MTTKRP of fit sweeps
@@ -209,20 +218,39 @@ void fill_prob(Prob& q, const cpd_desc* d) {
     if (q.n[m] > q.nmax) q.nmax = q.n[m];
 }
 
+// Whether the products can read the caller's X and Z in place: whole
+// 16-byte chunks along R_thc, aligned rows.
+bool inputs_in_place(const Prob& q) {
+  uintptr_t all = (uintptr_t)q.d.Z;
+  for (int m = 0; m < 4; ++m) all |= (uintptr_t)q.d.X[m];
+  return q.Rt % 2 == 0 && (all & 15) == 0;
+}
+
 template <typename T>
-void carve_typed(Layout& L, Prob& q, Bufs<T>& b, bool own_inputs) {
+void carve_typed(Layout& L, Prob& q, Bufs<T>& b) {
+  constexpr int V = 16 / (int)sizeof(T);
   const int Rt = q.Rt, Tp = q.Tp;
-  if (own_inputs) {
+  b.Kr = (Rt + V - 1) / V * V;
+  if (sizeof(T) == 8 && inputs_in_place(q)) {
+    b.ldx = Rt;
+    for (int m = 0; m < 4; ++m) b.X[m] = (const T*)q.d.X[m];
+    b.Z = (const T*)q.d.Z;
+  } else {
+    // copies in the plan's type, rows padded with zeros to whole chunks
+    b.ldx = b.Kr;
     for (int m = 0; m < 4; ++m) {
       int alias = -1;
       for (int r = 0; r < m; ++r)
         if (q.d.X[r] == q.d.X[m]) alias = r;
-      b.X[m] = alias >= 0 ? b.X[alias] : (const T*)L.take(sizeof(T) * (size_t)q.n[m] * Rt);
+      b.X[m] = alias >= 0 ? b.X[alias] : (const T*)L.take(sizeof(T) * (size_t)q.n[m] * b.ldx);
     }
-    b.Z = (const T*)L.take(sizeof(T) * (size_t)Rt * Rt);
+    b.Z = (const T*)L.take(sizeof(T) * (size_t)Rt * b.ldx);
   }
-  for (int m = 0; m < 4; ++m) b.W[m] = (T*)L.take(sizeof(T) * (size_t)Rt * Tp);
-  b.Y = (T*)L.take(sizeof(T) * (size_t)Rt * Tp);
+  // (rows Rt .. Kr - 1 stay zero)
+  for (int m = 0; m < 4; ++m) b.W[m] = (T*)L.take(sizeof(T) * (size_t)b.Kr * Tp);
+  b.Y = (T*)L.take(sizeof(T) * (size_t)b.Kr * Tp);
+  b.HP = (T*)L.take(sizeof(T) * (size_t)b.Kr * Tp);
+  b.BP = (T*)L.take(sizeof(T) * (size_t)b.Kr * Tp);
   b.Msol = (T*)L.take(sizeof(T) * (size_t)q.nmax * Tp);
   b.Msave = (T*)L.take(sizeof(T) * (size_t)q.n[3] * Tp);
   b.Mbak = (T*)L.take(sizeof(T) * (size_t)q.nmax * Tp);
@@ -317,11 +345,9 @@ void carve_prob(Layout& L, Prob& q, int prec, SplitShare& sh) {
   for (int i = 0; i < 3; ++i) q.setup[i] = (double*)L.take(sizeof(double) * setup_elems);
   q.scratch64 = (double*)L.take(sizeof(double) * (size_t)q.nmax * Tp);
   if (prec == CPD_FP32) {
-    carve_typed<float>(L, q, q.b32, true);
+    carve_typed<float>(L, q, q.b32);
   } else {
-    carve_typed<double>(L, q, q.b64, false);
-    for (int m = 0; m < 4; ++m) q.b64.X[m] = q.d.X[m];
-    q.b64.Z = q.d.Z;
+    carve_typed<double>(L, q, q.b64);
     if (prec == CPD_MIXED_BF16) carve_mixed(L, q, sh);
   }
 }
@@ -332,6 +358,12 @@ void carve_prob(Layout& L, Prob& q, int prec, SplitShare& sh) {
 struct TableBuilder {
   Layout L;
   std::vector<char> host;
+  // one region of partial tiles and one of counters serve all split
+  // products of a plan, which run one after the other on its stream
+  char* part = nullptr;
+  int32_t* cnt = nullptr;
+  size_t part_cap = (size_t)128 << 20, part_need = 0;
+  int cnt_cap = 1 << 16, cnt_need = 0;
   template <typename X>
   void* put(const std::vector<X>& v) {
     const size_t bytes = sizeof(X) * v.size();
@@ -351,37 +383,59 @@ std::string tune_key(const std::string& kind, const std::vector<int>& dims) {
   return k;
 }
 
+// Fills the split and layout fields of the entries for tile form bm and
+// returns the prefix sums of their workgroups.
 template <typename T>
-GroupOp gemm_op(TableBuilder& tb, const std::vector<GemmArgs<T>>& v, bool at, bool had, const std::string& kind) {
+std::vector<int> gemm_entries(TableBuilder& tb, std::vector<GemmArgs<T>>& v, int bm) {
+  size_t bytes = 0;
+  int cnts = 0;
+  auto need = [&](const GemmArgs<T>& g) { return g.slices > 1 ? gemm_tile_count(g.M, g.N, bm, g.lower) - g.nfull : 0; };
+  for (auto& g : v) {
+    bytes += sizeof(T) * (size_t)need(g) * g.slices * bm * bm;
+    cnts += need(g);
+  }
+  const bool fits = bytes <= tb.part_cap && cnts <= tb.cnt_cap;
+  if (fits && bytes > tb.part_need) tb.part_need = bytes;
+  if (fits && cnts > tb.cnt_need) tb.cnt_need = cnts;
+  std::vector<int> offs(1, 0);
+  size_t at = 0;
+  int c = 0;
+  for (auto& g : v) {
+    if (!fits) g.slices = 1;
+    const int t = need(g);
+    g.part = t ? tb.part + at : nullptr;
+    g.cnt = t ? tb.cnt + c : nullptr;
+    at += sizeof(T) * (size_t)t * g.slices * bm * bm;
+    c += t;
+    offs.push_back(offs.back() + gemm_units(g, bm));
+  }
+  return offs;
+}
+
+template <typename T>
+GroupOp gemm_op(TableBuilder& tb, std::vector<GemmArgs<T>> v, bool at, bool bt, const std::string& kind) {
   GroupOp op;
   op.a_t = at;
-  op.had = had;
-  // tile edge: autotune cache, else heuristic.  Register-staged tiles: 64
-  // (three workgroups per compute unit; the staged 128 x 128 form holds
-  // ~400 registers, one per unit), 128 only with thousands of tiles.
+  op.b_t = bt;
+  op.count = (int)v.size();
+  // the long products first, so that the launch does not end on one
+  std::stable_sort(v.begin(), v.end(), [](const GemmArgs<T>& x, const GemmArgs<T>& y) { return x.K > y.K; });
   std::vector<int> dims;
-  long t128 = 0;
   for (auto& g : v) {
+    gemm_plan_slices(g);
+    gemm_set_vec(g);
     dims.push_back(g.M);
     dims.push_back(g.N);
     dims.push_back(g.K);
-    t128 += gemm_tile_count(g.M, g.N, 128, g.lower);
   }
-  // FP64: 128 is the direct-load path (1.3-1.4x the 64-tiles at R = 4000),
-  // taken when every entry qualifies and the 128-tiles cover the compute
-  // units (the back-projection's 224 tiles at n = 800 stay on 64)
-  bool dma = sizeof(T) == 8;
-  for (auto& g : v) dma = dma && gemm_dma_ok(g, had);
-  op.bm = dma ? (t128 >= 256 ? 128 : 64) : (t128 >= 4096 ? 128 : 64);
-  op.count = (int)v.size();
+  // tile form: autotune cache, else the rule
+  op.bm = gemm_tile_form<T>(v);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(tune_key(kind, dims));
     if (it != g_tune.end()) op.bm = it->second;
   }
-  if (sizeof(T) == 8 && !dma) op.bm = 64;
-  std::vector<int> offs(1, 0);
-  for (auto& g : v) offs.push_back(offs.back() + gemm_tile_count(g.M, g.N, op.bm, g.lower));
+  const std::vector<int> offs = gemm_entries(tb, v, op.bm);
   op.total = offs.back();
   op.tab = tb.put(v);
   op.offs = (int*)tb.put(offs);
@@ -590,8 +644,7 @@ std::vector<SolveLaunch> build_sched(TableBuilder& tb, int sched, int max_nblk, 
           v.push_back(g);
         }
       }
-      L.gemm = gemm_op<T>(tb, v, false, false, kind + "panel");
-      L.gemm.b_t = bt;
+      L.gemm = gemm_op<T>(tb, v, false, bt, kind + "panel");
     }
     out.push_back(L);
   }
@@ -612,13 +665,41 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
       Bufs<T>& b = q.*bufs;
       const int32_t* done = &q.st->done;
       const int Rt = q.Rt, Rc = q.Rc, Tp = q.Tp;
-      if (n == 0) core.push_back({Rt, Rc, Rt, b.Z, Rt, b.W[2], b.W[3], Tp, b.Y, Tp, nullptr, T(1), T(0), done});
-      if (n == 2) core.push_back({Rt, Rc, Rt, b.Z, Rt, b.W[0], b.W[1], Tp, b.Y, Tp, nullptr, T(1), T(0), done});
-      back.push_back({q.n[n], Rc, Rt, b.X[n], Rt, b.W[partner_of[n]], b.Y, Tp, b.Msol, Tp,
+      const int p_ = partner_of[n];
+      // The pair operand of each product is formed by the product that
+      // completes it: W_p o Y by the core product (for modes 0 and 2) or the
+      // projection of mode 0 or 2 (for modes 1 and 3); W_a o W_b by the
+      // projection of mode 1 or 3.  In the tied model modes 1 and 3 are
+      // copies: with shared X the projections of modes 0 and 2 form the
+      // square for the next core product, and the projection of mode 2 also
+      // W_2 o Y' for the closing MTTKRP of mode 3.
+      if (n == 0 || n == 2) {
+        GemmArgs<T> g{Rt, Rc, n == 0 ? b.Kr : Rt, b.Z, b.ldx, b.HP, nullptr, Tp, b.Y, Tp, nullptr, T(1), T(0), done};
+        g.H1 = b.W[p_];
+        g.P1 = b.BP;
+        core.push_back(g);
+      }
+      back.push_back({q.n[n], Rc, b.Kr, b.X[n], b.ldx, b.BP, nullptr, Tp, b.Msol, Tp,
                       n == 3 ? b.Msave : nullptr, T(1), T(0), done});
       gram.push_back({Rc, Rc, q.n[n], b.F[n], Tp, b.F[n], nullptr, Tp, b.G[n], Tp, nullptr, T(1), T(0), done});
       gram.back().lower = 1;  // consumers read the lower triangle only
-      proj.push_back({Rt, Rc, q.n[n], b.X[n], Rt, b.F[n], nullptr, Tp, b.W[n], Tp, nullptr, T(1), T(0), done});
+      {
+        GemmArgs<T> g{Rt, Rc, q.n[n], b.X[n], b.ldx, b.F[n], nullptr, Tp, b.W[n], Tp, nullptr, T(1), T(0), done};
+        if (n == 1 || n == 3) {
+          g.H1 = b.W[p_];
+          g.P1 = b.HP;
+        } else {
+          if (!p->tied || n == 2) {
+            g.H1 = b.Y;
+            g.P1 = b.BP;
+          }
+          if (p->tied && p->tie_alias) {
+            g.H2 = b.W[n];
+            g.P2 = b.HP;
+          }
+        }
+        proj.push_back(g);
+      }
       if (gated) {
         // split-BF16 plans: these FP64 products serve only problems promoted
         // to the FP64 path (the Gram always runs in FP64)
@@ -636,10 +717,13 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
       fv.push_back({b.V, g[0], g[1], g[2], q.st, Tp, Rc});
       nm.push_back({b.Msol, b.F[n], b.lam, nullptr, nullptr, q.st, q.n[n], Rc, Tp});
     }
-    if (n == 0 || n == 2) p->core[n] = gemm_op<T>(tb, core, n == 2, true, kind + "core");
-    p->back[n] = gemm_op<T>(tb, back, false, true, kind + "back");
+    if (n == 0 || n == 2) p->core[n] = gemm_op<T>(tb, core, n == 2, false, kind + "core");
+    p->back[n] = gemm_op<T>(tb, back, false, false, kind + "back");
     p->gram[n] = gemm_op<T>(tb, gram, true, false, kind + "gram");
     p->proj[n] = gemm_op<T>(tb, proj, true, false, kind + "proj");
+    std::vector<GemmArgs<T>> both(gram);
+    both.insert(both.end(), proj.begin(), proj.end());
+    p->gramproj[n] = gemm_op<T>(tb, both, true, false, kind + "gramproj");
     StepOps& so = p->steps[n];
     so.probs = tb.put(sp);
     const int pw = p->panel_width > 0 ? p->panel_width : p->maxNblk;
@@ -795,23 +879,50 @@ void build_mixed(TableBuilder& tb, cpd_plan_s* p) {
     const int32_t* done = &q.st->done;
     const int32_t* path = &q.st->path;
     const int Rt = q.Rt, Rc = q.Rc, Tp = q.Tp;
-    for (int m = 0; m < 3; ++m)
-      fp[m].push_back({Rt, Rc, q.n[m], b.X[m], Rt, b.F[m], nullptr, Tp, b.W[m], Tp, nullptr, 1.0, 0.0, done, path, 0});
-    fc.push_back({Rt, Rc, Rt, b.Z, Rt, b.W[0], b.W[1], Tp, b.Y, Tp, nullptr, 1.0, 0.0, done, path, 0});
-    fb.push_back({q.n[3], Rc, Rt, b.X[3], Rt, b.W[2], b.Y, Tp, b.Msave, Tp, nullptr, 1.0, 0.0, done, path, 0});
-    for (int m = 0; m < 4; ++m)
-      cp[m].push_back({Rt, Rc, q.n[m], b.X[m], Rt, b.F[m], nullptr, Tp, b.W[m], Tp, nullptr, 1.0, 0.0, done,
-                       &q.st->promote, 1});
+    const int Kr = b.Kr, ldx = b.ldx;
+    auto proj = [&](int m) {
+      return GemmArgs<double>{Rt, Rc, q.n[m], b.X[m], ldx, b.F[m], nullptr, Tp, b.W[m], Tp, nullptr, 1.0, 0.0, done};
+    };
+    for (int m = 0; m < 3; ++m) {
+      GemmArgs<double> g = proj(m);
+      g.gate = path;
+      if (m == 1) {
+        g.H1 = b.W[0];
+        g.P1 = b.HP;
+      }
+      fp[m].push_back(g);
+    }
+    GemmArgs<double> g{Rt, Rc, Rt, b.Z, ldx, b.HP, nullptr, Tp, b.Y, Tp, nullptr, 1.0, 0.0, done, path, 0};
+    g.H1 = b.W[2];
+    g.P1 = b.BP;
+    fc.push_back(g);
+    fb.push_back({q.n[3], Rc, Kr, b.X[3], ldx, b.BP, nullptr, Tp, b.Msave, Tp, nullptr, 1.0, 0.0, done, path, 0});
+    for (int m = 0; m < 4; ++m) {
+      GemmArgs<double> c = proj(m);
+      c.gate = &q.st->promote;
+      c.want = 1;
+      if (m == 3) {
+        c.H1 = b.W[2];
+        c.P1 = b.HP;
+      }
+      cp[m].push_back(c);
+    }
   }
   for (int m = 0; m < 3; ++m) p->fproj[m] = gemm_op<double>(tb, fp[m], true, false, "f64proj");
-  p->fcore = gemm_op<double>(tb, fc, true, true, "f64core");
-  p->fback = gemm_op<double>(tb, fb, false, true, "f64back");
+  p->fcore = gemm_op<double>(tb, fc, true, false, "f64core");
+  p->fback = gemm_op<double>(tb, fb, false, false, "f64back");
   for (int m = 0; m < 4; ++m) p->cproj[m] = gemm_op<double>(tb, cp[m], true, false, "f64proj");
 }
 
 size_t build_tables(cpd_plan_s* p, char* base, std::vector<char>* host) {
   TableBuilder tb;
   tb.L.base = base;
+  if (base) {
+    tb.part = p->ws + p->part_off;
+    tb.part_cap = p->part_bytes;
+    tb.cnt = (int32_t*)(p->ws + p->cnt_off);
+    tb.cnt_cap = p->cnt_count;
+  }
   if (p->prec == CPD_FP32) build_typed<float>(tb, p, &Prob::b32, false);
   else build_typed<double>(tb, p, &Prob::b64, p->prec == CPD_MIXED_BF16);
   if (p->prec == CPD_MIXED_BF16) build_mixed(tb, p);
@@ -824,19 +935,24 @@ size_t build_tables(cpd_plan_s* p, char* base, std::vector<char>* host) {
     tb.host.resize(tb.L.off);
     *host = tb.host;
   }
+  if (!base) {
+    p->part_bytes = align_up(tb.part_need);
+    p->cnt_count = tb.cnt_need;
+  }
   return tb.L.off;
 }
 
-// Carves all problems and sizes the table region; returns total bytes
-// (the last 4 KiB are autotuning scratch).
+// Carves all problems and sizes the table region, then the partial tiles
+// and counters of the split products; returns total bytes.
 size_t layout_plan(cpd_plan_s* p, char* base) {
   Layout L;
   L.base = base;
   SplitShare sh;
   for (auto& q : p->P) carve_prob(L, q, p->prec, sh);
   p->tables_off = L.off;
-  const size_t tables = build_tables(p, nullptr, nullptr);
-  return L.off + align_up(tables) + 4096;
+  p->cnt_off = L.off + align_up(build_tables(p, nullptr, nullptr));
+  p->part_off = p->cnt_off + align_up(sizeof(int32_t) * (size_t)p->cnt_count);
+  return p->part_off + p->part_bytes;
 }
 
 int init_shape(cpd_plan_s* p, const cpd_desc* descs, int count) {
@@ -879,6 +995,23 @@ int init_shape(cpd_plan_s* p, const cpd_desc* descs, int count) {
 }
 
 // ------------------------------------------------------------------ set-up
+// The plan's own copies of X and Z (FP32, or rows that are no whole 16-byte
+// chunks); the padding of their rows is zero already.
+template <typename T>
+void copy_inputs_typed(const Prob& q, const Bufs<T>& b, hipStream_t s) {
+  for (int m = 0; m < 4; ++m) {
+    bool first = (const void*)b.X[m] != (const void*)q.d.X[m];
+    for (int r = 0; r < m; ++r)
+      if (b.X[r] == b.X[m]) first = false;
+    if (first) copy_rows_f64<T>(s, q.d.X[m], q.n[m], q.Rt, (T*)b.X[m], b.ldx);
+  }
+  if ((const void*)b.Z != (const void*)q.d.Z) copy_rows_f64<T>(s, q.d.Z, q.Rt, q.Rt, (T*)b.Z, b.ldx);
+}
+void copy_inputs(cpd_plan_s* p, const Prob& q, hipStream_t s) {
+  if (p->prec == CPD_FP32) copy_inputs_typed<float>(q, q.b32, s);
+  else copy_inputs_typed<double>(q, q.b64, s);
+}
+
 int setup_norm2(Prob& q, hipStream_t s) {
   if (q.d.norm2) {  // supplied by the caller (a DF input: ||B^T B||_F^2)
     HIPCHK(hipMemcpyAsync(q.norm2, q.d.norm2, sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -941,7 +1074,7 @@ void split_inputs(Prob& q, hipStream_t s, std::map<const void*, int>& done_split
 template <typename T>
 void run_gemm(cpd_plan_s* p, hipStream_t s, const GroupOp& op) {
   (void)p;
-  gemm_group<T>(s, (const GemmArgs<T>*)op.tab, op.offs, op.count, op.total, op.a_t, op.b_t, op.had, op.bm);
+  gemm_group<T>(s, (const GemmArgs<T>*)op.tab, op.offs, op.count, op.total, op.a_t, op.b_t, op.bm);
 }
 void run_split(cpd_plan_s* p, hipStream_t s, const GroupOp& op) {
   (void)p;
@@ -1007,8 +1140,7 @@ void enqueue_sweep_tied(cpd_plan_s* p, hipStream_t s, bool fast) {
     run_gemm<T>(p, s, p->core[n]);
     run_gemm<T>(p, s, p->back[n]);
     solve_mode<T>(p, n, s, false, fast);
-    run_gemm<T>(p, s, p->gram[n]);
-    run_gemm<T>(p, s, p->proj[n]);
+    run_gemm<T>(p, s, p->gramproj[n]);
     checkpoint_group(s, (const CkptArgs*)p->tie[n / 2], p->count, 0);
     if (!p->tie_alias) run_gemm<T>(p, s, p->proj[n + 1]);
   }
@@ -1029,8 +1161,7 @@ void enqueue_sweep_typed(cpd_plan_s* p, hipStream_t s, bool fast) {
     if (n == 0 || n == 2) run_gemm<T>(p, s, p->core[n]);
     run_gemm<T>(p, s, p->back[n]);
     solve_mode<T>(p, n, s, n == 3, fast);
-    run_gemm<T>(p, s, p->gram[n]);
-    run_gemm<T>(p, s, p->proj[n]);
+    run_gemm<T>(p, s, p->gramproj[n]);
   }
   fit_group<T>(s, (const FitArgs<T>*)p->fit, p->count, p->maxR, HIST_CAP, p->tol, p->fit_floor, 0, 0.0,
                p->fit_every);
@@ -1041,8 +1172,8 @@ void enqueue_sweep_typed(cpd_plan_s* p, hipStream_t s, bool fast) {
 // (from the FP64 factors) for <G, G~>: the residual is first-order
 // sensitive to that inner product, which split BF16 cannot deliver.
 void mixed_refresh_mode(cpd_plan_s* p, hipStream_t s, int n, bool with_gram = true) {
-  if (with_gram) run_gemm<double>(p, s, p->gram[n]);
-  run_gemm<double>(p, s, p->proj[n]);  // FP64-path problems only (gated)
+  // (the projection: FP64-path problems only, gated)
+  run_gemm<double>(p, s, with_gram ? p->gramproj[n] : p->proj[n]);
   int maxc = 0, maxd = 0;
   for (auto& q : p->P) {
     if (q.Rc > maxc) maxc = q.Rc;
@@ -1099,11 +1230,9 @@ bool is_fit_sweep(const cpd_plan_s* p, long index1) {
 int refresh_all(cpd_plan_s* p, hipStream_t s) {
   for (int m = 0; m < 4; ++m) {
     if (p->prec == CPD_FP64) {
-      run_gemm<double>(p, s, p->gram[m]);
-      run_gemm<double>(p, s, p->proj[m]);
+      run_gemm<double>(p, s, p->gramproj[m]);
     } else if (p->prec == CPD_FP32) {
-      run_gemm<float>(p, s, p->gram[m]);
-      run_gemm<float>(p, s, p->proj[m]);
+      run_gemm<float>(p, s, p->gramproj[m]);
     } else {
       mixed_refresh_mode(p, s, m);
     }
@@ -1253,9 +1382,15 @@ void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
     (void)hipEventDestroy(e0);
     return;
   }
-  int* doffs = (int*)(p->ws + p->ws_bytes - 4096);
+  // the tables are rebuilt after the tuning, so a candidate's entries and
+  // prefix sums are written over the op's own
+  TableBuilder tb;
+  tb.part = p->ws + p->part_off;
+  tb.part_cap = p->part_bytes;
+  tb.cnt = (int32_t*)(p->ws + p->cnt_off);
+  tb.cnt_cap = p->cnt_count;
   auto tune = [&](GroupOp& op, const std::string& kind) {
-    if (op.total == 0 || !op.tab || (size_t)(op.count + 1) * sizeof(int) > 4096) return;
+    if (op.total == 0 || !op.tab) return;
     std::vector<GemmArgs<T>> host(op.count);
     if (hipMemcpy(host.data(), op.tab, sizeof(GemmArgs<T>) * op.count, hipMemcpyDeviceToHost) != hipSuccess)
       return;
@@ -1276,18 +1411,19 @@ void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
     }
     float best = 1e30f;
     int best_bm = op.bm;
-    bool dma = sizeof(T) == 8;
-    for (auto& g : host) dma = dma && gemm_dma_ok(g, op.had);
-    for (int bm : {64, 128}) {
-      if (bm == 128 && sizeof(T) == 8 && !dma) continue;
-      std::vector<int> offs(1, 0);
-      for (auto& g : host) offs.push_back(offs.back() + gemm_tile_count(g.M, g.N, bm, g.lower));
-      if (hipMemcpy(doffs, offs.data(), sizeof(int) * offs.size(), hipMemcpyHostToDevice) != hipSuccess) return;
+    bool tail = false;
+    for (auto& g : host) tail = tail || (g.slices > 1 && g.nfull > 0);
+    for (int bm : {32, 64, 128}) {
+      if (tail && bm != 64) continue;  // (its split is made for 64-tiles)
+      std::vector<GemmArgs<T>> v(host);
+      const std::vector<int> offs = gemm_entries(tb, v, bm);
+      if (hipMemcpy(op.tab, v.data(), sizeof(GemmArgs<T>) * v.size(), hipMemcpyHostToDevice) != hipSuccess) return;
+      if (hipMemcpy(op.offs, offs.data(), sizeof(int) * offs.size(), hipMemcpyHostToDevice) != hipSuccess) return;
       float ms = 0.f;
       for (int w = 0; w < 2; ++w) {  // second pass is the timed one
         (void)hipEventRecord(e0, s);
         for (int r = 0; r < 3; ++r)
-          gemm_group<T>(s, (const GemmArgs<T>*)op.tab, doffs, op.count, offs.back(), op.a_t, op.b_t, op.had, bm);
+          gemm_group<T>(s, (const GemmArgs<T>*)op.tab, op.offs, op.count, offs.back(), op.a_t, op.b_t, bm);
         (void)hipEventRecord(e1, s);
         (void)hipEventSynchronize(e1);
         (void)hipEventElapsedTime(&ms, e0, e1);
@@ -1306,6 +1442,7 @@ void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
     if (!gram_only && (n == 0 || n == 2)) tune(p->core[n], kind + "core");
     if (!gram_only) tune(p->back[n], kind + "back");
     tune(p->gram[n], kind + "gram");
+    tune(p->gramproj[n], kind + "gramproj");
     if (!gram_only) tune(p->proj[n], kind + "proj");
   }
   (void)hipEventDestroy(e0);
@@ -1417,6 +1554,8 @@ int plan_create(const cpd_desc* descs, int count, void* workspace, size_t ws_byt
   }
   hipStream_t s = p->stream;
   fill_bytes(s, workspace, p->tables_off);
+  fill_bytes(s, p->ws + p->cnt_off, sizeof(int32_t) * (size_t)p->cnt_count);
+  for (auto& q : p->P) copy_inputs(p, q, s);
   rc = upload_tables(p, s);
   if (rc == CPD_OK && p->autotune) {
     // tuning launches write the plan's intermediate buffers; they are
@@ -1431,6 +1570,7 @@ int plan_create(const cpd_desc* descs, int count, void* workspace, size_t ws_byt
     }
     rc = upload_tables(p, s);
     fill_bytes(s, workspace, p->tables_off);
+    for (auto& q : p->P) copy_inputs(p, q, s);
   }
   std::map<const void*, int> split_done;
   for (int i = 0; i < count && rc == CPD_OK; ++i) {
@@ -1438,13 +1578,6 @@ int plan_create(const cpd_desc* descs, int count, void* workspace, size_t ws_byt
     rc = setup_norm2(q, s);
     if (rc != CPD_OK) break;
     if (p->prec == CPD_FP32) {
-      for (int m = 0; m < 4; ++m) {
-        bool first = true;
-        for (int r = 0; r < m; ++r)
-          if (q.d.X[r] == q.d.X[m]) first = false;
-        if (first) cast_f64_to_f32(s, q.d.X[m], (float*)q.b32.X[m], (size_t)q.n[m] * q.Rt);
-      }
-      cast_f64_to_f32(s, q.d.Z, (float*)q.b32.Z, (size_t)q.Rt * q.Rt);
       for (int m = 0; m < 4; ++m) {
         // (tied: modes 1 and 3 start as copies of modes 0 and 2)
         copy_normalised_init(s, q.d.init[p->tied ? m & 2 : m], q.n[m], q.Rc, q.Tp, q.scratch64);
@@ -1536,6 +1669,19 @@ int batch_sweep(cpd_plan_s* p, int nsweeps, double* fits_host, int32_t* n_run) {
   if (n_run) *n_run = ran;
   if (sync) return batch_status(p);
   return CPD_OK;
+}
+
+// MTTKRP of any mode from the current projections.  The pair operands that
+// a sweep forms along the way are formed here, and the one that the next
+// sweep starts from is put back.
+template <typename T>
+void mttkrp_typed(cpd_plan_s* p, hipStream_t s, const Bufs<T>& b, int Tp, int core, int mode) {
+  const size_t count = (size_t)b.Kr * Tp;
+  if (core == 2) hadamard<T>(s, b.W[0], b.W[1], b.HP, count);
+  run_gemm<T>(p, s, p->core[core]);
+  hadamard<T>(s, b.W[partner_of[mode]], b.Y, b.BP, count);
+  run_gemm<T>(p, s, p->back[mode]);
+  if (core == 2) hadamard<T>(s, b.W[2], b.W[3], b.HP, count);
 }
 
 int stats_of(cpd_plan_s* p, int idx, cpd_stats_t* out) {
@@ -1699,12 +1845,10 @@ cpd_status cpd_mttkrp(cpd_plan p, int32_t mode, double* M_dev) {
   const int core = mode < 2 ? 0 : 2;
   Prob& q = p->P[0];
   if (p->prec == CPD_FP64) {
-    run_gemm<double>(p, s, p->core[core]);
-    run_gemm<double>(p, s, p->back[mode]);
+    mttkrp_typed<double>(p, s, q.b64, q.Tp, core, mode);
     return copy_out(p, q, q.b64.Msol, q.n[mode], q.Rc, M_dev, s);
   } else if (p->prec == CPD_FP32) {
-    run_gemm<float>(p, s, p->core[core]);
-    run_gemm<float>(p, s, p->back[mode]);
+    mttkrp_typed<float>(p, s, q.b32, q.Tp, core, mode);
     return copy_out(p, q, q.b32.Msol, q.n[mode], q.Rc, M_dev, s);
   }
   run_split(p, s, p->score[core]);

@@ -1,17 +1,18 @@
-// Dense GEMM on the 16x16x4 FP64 / FP32 matrix cores, with the Hadamard
-// product of two B operands fused into the operand load.
+// Dense GEMM on the 16x16x4 FP64 / FP32 matrix cores.
 //
-// This one kernel family carries every contraction of the matrix-free
-// MTTKRP (projection X^T F, core product Z (W o W), back-projection
-// X (W o Y)), the Gram matrices F^T F and the set-up products.
+// This one kernel family carries every FP64 / FP32 contraction of the
+// matrix-free MTTKRP (projection X^T F, core product Z (W o W),
+// back-projection X (W o Y)), the Gram matrices F^T F, the set-up products
+// and the FP32 layers of the warm-start network.
 //
-// Two forms, 256 threads = 2 x 2 waves each:
-//   - register-staged (any shape, FP64 and FP32): block tile BM x BN (64 or
-//     128), k-step 16 staged through LDS in k-major form, the next k-tile
-//     prefetched into registers while the current one is multiplied;
-//   - direct-load (FP64, qualifying shapes, gemm_dma_ok): 128 x 128 tiles
-//     loaded from global memory straight into a two-stage LDS pipeline,
-//     which keeps two workgroups per compute unit (below).
+// Two forms:
+//   - direct-load tiles (FP64 and FP32, gemm_tile_ok): operands go from
+//     global memory straight into LDS, and are read from there 16 bytes a
+//     lane (below).  Every product of a plan takes this form.
+//   - register-staged 64 x 64 tiles, 256 threads = 2 x 2 waves, k-step 16
+//     through LDS in k-major form, the next k-tile prefetched into
+//     registers: single products of any shape and alignment, and products
+//     with a Hadamard pair operand.
 #include "kernels.h"
 #include "mfma.h"
 
@@ -188,211 +189,488 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs<T> p) {
   gemm_body<T, BM, BN, AT, BT, HAD>(p, blockIdx.x, gridDim.x);
 }
 
-// Grouped form: workgroup -> (problem, local tile) through the prefix sums.
-// The FP64 64-tiles fit four workgroups per compute unit (<= 128
-// registers, the accumulators in VGPRs; with a Hadamard operand a few
-// values spill): the lower-triangle Gram at R = 4000 is then ~2 rounds of
-// its 2016 tiles, and the back-projection's 819 tiles at n = 800 all
-// resident at once.
-template <typename T, int BM, int BN, bool AT, bool BT, bool HAD>
-__global__ __launch_bounds__(256, (BM == 64 && sizeof(T) == 8) ? 4 : 1) void gemm_group_kernel(
-    const GemmArgs<T>* tab, const int* offs, int nprob) {
-  int pid = 0;
-  while (pid + 1 < nprob && (int)blockIdx.x >= offs[pid + 1]) ++pid;
-  const GemmArgs<T> p = tab[pid];
-  gemm_body<T, BM, BN, AT, BT, HAD>(p, blockIdx.x - offs[pid], offs[pid + 1] - offs[pid]);
-}
 
 // ---------------------------------------------------------------------
-// FP64 with 128 x 128 block tiles and direct global -> LDS loads
-// (global_load_lds_dwordx4): no register staging, so the accumulators (64
-// per lane, in AGPRs) and the fragments fit two workgroups per compute unit
-// (~200 registers, 52-72 KB LDS with two stages), where the register-staged
-// 128 x 128 form holds ~400 registers and one workgroup.  One barrier per
-// k-step: the next k-tile is in flight while the current one is multiplied.
-// LDS layouts (a wave instruction writes 64 consecutive 16-byte chunks):
-//   - operand contiguous along its row index r (k-major, element (k, r) at
-//     base[k ld + r]): row k of the tile, 128 doubles, at stage + k * 144
-//     (the padding puts rows k and k + 1 in different banks);
-//   - operand contiguous along k (element (r, k) at base[r ld + k]): k-pair
-//     major, [k / 2][r][k % 2], so a fragment read of 16 consecutive r is
-//     conflict-free.
-// Rows or columns past the matrix edge read a clamped in-range address;
-// they only feed result elements that are not stored.  Requirements (checked
-// on the host, gemm_dma_ok): beta = 0, a full (not lower-triangle) result,
-// K a multiple of the k-step (8 with a Hadamard operand pair, 16
-// otherwise), even leading dimensions, 16-byte aligned operands.  (The
-// lower-triangle Gram is faster on the 64-tiles: the 128-tiles on the
-// diagonal would compute twice the needed elements.)
+// Direct-load tiles.  BM x BN tiles, WM x WN waves, k-steps of BKB bytes
+// of k (128: 16 doubles or 32 floats), ST LDS stages of which ST - 1 are in
+// flight while one is multiplied.  buffer_load_dwordx4 ... lds moves 16
+// bytes a lane (V = 2 doubles or 4 floats) without staging registers; a
+// lane past the end of K reads an offset outside the buffer's bound, which
+// writes zeros, so K needs no multiple of the k-step.  Rows past the edge
+// read a clamped in-range address and feed only elements that are not
+// stored.
+//
+// What bounds it: the FP64 matrix instruction takes 64 cycles, so 16 of
+// them (a 64 x 64 wave tile and 4 of k) leave ~1000 cycles for a few LDS
+// reads; the loss is in waits.  So:
+//   - one barrier per k-step, with a plain s_barrier (a fenced one would
+//     wait for the loads of the next stages);
+//   - few LDS reads without bank conflicts.  An operand contiguous along
+//     its row index r is kept as [k][r]; one 16-byte read of a lane brings
+//     V adjacent rows, which feed V different 16-row tiles (tile a of a
+//     group of V holds rows V i + a, i = 0..15), so that a lane's results
+//     are adjacent columns of C as well.  An operand contiguous along k is
+//     kept as [r][k] with the 16-byte chunks of a row XORed by r: the 16
+//     rows of a read then lie in 16 different chunks of the banks;
+//   - the fragments of the next 4 of k are read before the products of the
+//     present ones.
+// Every tile form adds the products of one element in the order of k, four
+// to an instruction, as the register-staged form does: a result depends
+// neither on the tile form nor on the path.
+//
+// Measured on the MI355X (FP64): 4096^3 63-66 TFLOP/s with 64 x 64 tiles,
+// 70.6 with 128 x 128 tiles of eight waves (66.5 at 4000^3, two rounds of
+// 512); the register-to-LDS form before it reached 49 with a Hadamard pair
+// and 59 without.  500 x 400 x 500: 46 us -> 22 us with 64 x 64 tiles (56
+// workgroups), 10.5 us with 32 x 32 tiles (208 workgroups, four stages in
+// flight).  FP32: 1000^3 62 us -> 26 us.
+//
+// Split K: a tile at or past nfull is computed by `slices` workgroups.
+// Each stores its partial tile device-coherently and then counts itself;
+// the last one sums the partial tiles in slice order, whichever it is, so
+// the result is reproducible, and sets the counter back to zero.  Nobody
+// waits for anybody.
 namespace {
-constexpr int DM = 128, DROW = 144;
+template <typename T>
+struct Chunk;
+template <>
+struct Chunk<double> {
+  static constexpr int V = 2;
+  typedef double vec __attribute__((ext_vector_type(2)));
+};
+template <>
+struct Chunk<float> {
+  static constexpr int V = 4;
+  typedef float vec __attribute__((ext_vector_type(4)));
+};
 typedef __attribute__((address_space(3))) void* lds_vptr;
-typedef const __attribute__((address_space(1))) void* glb_cvptr;
 }  // namespace
 
-template <bool KMAJOR, int BKD>
-__device__ __forceinline__ void dma_operand(const double* base, int ld, int r0, int rows, int k0, double* stage,
-                                            int w, int lane) {
-#pragma unroll
-  for (int i = 0; i < BKD / 4; ++i) {
-    const int idx = w * (BKD / 4) + i;
-    const double* g;
-    double* dst;
-    if (KMAJOR) {
-      const int r = min(r0 + 2 * lane, (rows - 1) & ~1);
-      g = base + (size_t)(k0 + idx) * ld + r;
-      dst = stage + idx * DROW;
-    } else {
-      const int kp = idx >> 1, half = idx & 1;
-      const int r = min(r0 + half * 64 + lane, rows - 1);
-      g = base + (size_t)r * ld + k0 + 2 * kp;
-      dst = stage + kp * (2 * DM) + half * 64 * 2;
-    }
-    __builtin_amdgcn_global_load_lds((glb_cvptr)g, (lds_vptr)dst, 16, 0, 0);
-  }
-}
-template <bool KMAJOR>
-__device__ __forceinline__ double dma_frag(const double* st, int r, int k) {
-  return KMAJOR ? st[k * DROW + r] : st[(k >> 1) * (2 * DM) + r * 2 + (k & 1)];
+// Tile forms.
+struct TileBig {    // 128 x 128, eight waves of 32 x 64, two workgroups per compute unit
+  static constexpr int BM = 128, BN = 128, WM = 4, WN = 2, BKB = 128, ST = 2, WPE = 4;
+};
+struct TileMid {    // 64 x 64, four waves of 32 x 32, four or five workgroups per compute unit
+  static constexpr int BM = 64, BN = 64, WM = 2, WN = 2, BKB = 128, ST = 2, WPE = 4;
+};
+struct TileSmall {  // 32 x 32, four waves of 16 x 16, long k-steps, four stages
+  static constexpr int BM = 32, BN = 32, WM = 2, WN = 2, BKB = 256, ST = 4, WPE = 2;
+};
+
+// Chunk c of row r of a k-contiguous operand lies in slot c ^ chunk_swizzle(r)
+// of the row (8 or 16 chunks: half or the whole of the 64 banks).
+template <int KP>
+__device__ __forceinline__ int chunk_swizzle(int r) {
+  static_assert(KP == 8 || KP == 16, "128- or 256-byte rows");
+  return KP == 8 ? (r >> 1) & 7 : r & 15;
 }
 
-template <bool AT, bool BT, bool HAD>
-__device__ __forceinline__ void gemm_dma_body(const GemmArgs<double>& p, int bid_in, int nblocks) {
-  constexpr int BKD = HAD ? 8 : 16;
-  constexpr int OPK = BKD * DROW, OPM = (BKD / 2) * DM * 2;
-  constexpr int SA = AT ? OPK : OPM, SB = BT ? OPM : OPK;
-  constexpr int STAGE = SA + SB * (HAD ? 2 : 1);
-  __shared__ __attribute__((aligned(16))) double lds[2 * STAGE];
+// The share of one thread in the loads of an operand tile of R rows.
+template <typename T, int R, int BK, bool KC, int NT>
+struct OperandLoad {
+  static constexpr int V = Chunk<T>::V;
+  static constexpr int KP = BK / V;  // 16-byte chunks of one row along k
+  static constexpr int PER = R * BK / V / NT;
+  static_assert(PER * NT * V == R * BK, "whole loads");
+  uint32_t off[PER];
+  int kof[PER];
+  __device__ __forceinline__ void init(int r0, int rows, int ld, int tid) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int c = i * NT + tid;
+      if (KC) {
+        const int r = c / KP, kp = (c % KP) ^ chunk_swizzle<KP>(r);
+        off[i] = (uint32_t)(((size_t)(min(r0 + r, rows - 1) - r0) * ld + kp * V) * sizeof(T));
+        kof[i] = kp * V;
+      } else {
+        const int k = c / (R / V), rv = c % (R / V);
+        off[i] = (uint32_t)(((size_t)k * ld + (min(r0 + rv * V, (rows - 1) / V * V) - r0)) * sizeof(T));
+        kof[i] = k;
+      }
+    }
+  }
+  // base: the operand at (r0, k0); left: the k's from k0 on (none: zeros)
+  __device__ __forceinline__ void issue(const T* base, int left, T* stage, int w) const {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7ffffff0, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_vptr)(stage + (size_t)(i * NT + w * 64) * V), 16,
+                                               kof[i] < left ? off[i] : 0xfffffff0u, 0, 0, 0);
+  }
+};
+
+// The fragments of one operand for the 16-row tiles of a wave.
+template <typename T, int R, int BK, bool KC, int TI>
+struct OperandFrag {
+  static constexpr int V = Chunk<T>::V;
+  static constexpr int F = KC ? 1 : (TI < V ? TI : V);  // tiles fed by one read
+  typedef T vr __attribute__((ext_vector_type(F)));
+  // k's 4 q .. 4 q + 3 of the stage, rows from r0 on
+  static __device__ __forceinline__ void read(T f[TI], const T* stage, int q, int r0, int lane) {
+    const int k = 4 * q + (lane >> 4), l = lane & 15;
+    if constexpr (KC) {
+      constexpr int KP = BK / V;
+#pragma unroll
+      for (int a = 0; a < TI; ++a) {
+        const int r = r0 + 16 * a + l;
+        f[a] = stage[(r * KP + ((k / V) ^ chunk_swizzle<KP>(r))) * V + k % V];
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < TI; a += F) {
+        const vr v = *(const vr*)(stage + k * R + r0 + 16 * a + F * l);
+#pragma unroll
+        for (int i = 0; i < F; ++i) f[a + i] = v[i];
+      }
+    }
+  }
+  // row (from r0) of index i (0..15) of tile a
+  static __device__ __forceinline__ int row(int a, int i) { return a / F * (16 * F) + i * F + a % F; }
+};
+
+template <typename T, typename C, bool AT, bool BT>
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int BM = C::BM, BN = C::BN, ST = C::ST, NT = 64 * C::WM * C::WN, V = Chunk<T>::V;
+  constexpr int BK = C::BKB / (int)sizeof(T);
+  constexpr int WTM = BM / C::WM, WTN = BN / C::WN, TI = WTM / 16, TJ = WTN / 16;
+  constexpr int SA = BM * BK, STG = SA + BN * BK;
+  typedef typename Acc4<T>::type acc_t;
+  typedef OperandLoad<T, BM, BK, !AT, NT> LoadA;
+  typedef OperandLoad<T, BN, BK, BT, NT> LoadB;
+  typedef OperandFrag<T, BM, BK, !AT, TI> FragA;
+  typedef OperandFrag<T, BN, BK, BT, TJ> FragB;
+  constexpr int LPS = LoadA::PER + LoadB::PER;  // loads of a wave per stage
+  __shared__ __attribute__((aligned(1024))) T lds[ST * STG];
+  __shared__ int last;
 
   if (p.done && *p.done) return;
   if (p.gate && *p.gate != p.want) return;
-  const int tiles_n = (p.N + DM - 1) / DM;
-  const int bid = xcd_remap(bid_in, nblocks);
-  int tm, tn;
-  grouped_tile(bid, (p.M + DM - 1) / DM, tiles_n, 8, tm, tn);
-  const int m0 = tm * DM, n0 = tn * DM;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  // C = (alpha A) B; beta must be 0 (gemm_dma_ok): any read of C here kept
-  // the accumulators out of the AGPRs and cost the second workgroup per unit
-  const gptr<double> gC = as_global(p.C), gC2 = as_global(p.C2);
-  const double alpha = p.alpha;
-  d4_t acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = d4_t{0, 0, 0, 0};
-  auto issue = [&](int kt, int s) {
-    double* st = lds + s * STAGE;
-    dma_operand<AT, BKD>(p.A, p.lda, m0, p.M, kt * BKD, st, w, lane);
-    dma_operand<!BT, BKD>(p.B1, p.ldb, n0, p.N, kt * BKD, st + SA, w, lane);
-    if constexpr (HAD) dma_operand<!BT, BKD>(p.B2, p.ldb, n0, p.N, kt * BKD, st + SA + SB, w, lane);
+  const int tiles_n = (p.N + BN - 1) / BN, tiles_m = (p.M + BM - 1) / BM;
+  const bool lower = p.lower && p.M == p.N;
+  const int ntiles = lower ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  const int nfull = p.slices > 1 ? p.nfull : ntiles;
+  // unsplit tiles first, then the slices of the others
+  int tile, slice = 0, kbeg = 0, kend = p.K;
+  if (local < nfull) {
+    tile = xcd_remap(local, nfull);
+  } else {
+    tile = nfull + (local - nfull) / p.slices;
+    slice = (local - nfull) % p.slices;
+    kbeg = gemm_slice_k(p.K, p.slices, slice);
+    kend = gemm_slice_k(p.K, p.slices, slice + 1);
+  }
+  int m0, n0;
+  if (lower) {
+    // the lower tiles in row order (row r holds r + 1)
+    int r = (int)((sqrtf(8.f * (float)tile + 1.f) - 1.f) * 0.5f);
+    while ((r + 1) * (r + 2) / 2 <= tile) ++r;
+    while (r * (r + 1) / 2 > tile) --r;
+    m0 = r * BM;
+    n0 = (tile - r * (r + 1) / 2) * BN;
+  } else {
+    int tm, tn;
+    grouped_tile(tile, tiles_m, tiles_n, 8, tm, tn);
+    m0 = tm * BM;
+    n0 = tn * BN;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
+  const int wm = w / C::WN, wn = w % C::WN;
+
+  LoadA la;
+  LoadB lb;
+  la.init(m0, p.M, p.lda, tid);
+  lb.init(n0, p.N, p.ldb, tid);
+  const size_t strideA = AT ? (size_t)BK * p.lda : BK, strideB = BT ? BK : (size_t)BK * p.ldb;
+  const T* gA = AT ? p.A + (size_t)kbeg * p.lda + m0 : p.A + (size_t)m0 * p.lda + kbeg;
+  const T* gB = BT ? p.B1 + (size_t)n0 * p.ldb + kbeg : p.B1 + (size_t)kbeg * p.ldb + n0;
+  const int nk = (kend - kbeg + BK - 1) / BK;
+  int left = kend - kbeg, wst = 0;
+  // past the last k-tile the loads bring zeros into a stage nobody reads,
+  // which keeps the wait counts constant
+  auto issue = [&]() {
+    la.issue(gA, left, lds + wst * STG, w);
+    lb.issue(gB, left, lds + wst * STG + SA, w);
+    left -= BK;
+    if (left > 0) {
+      gA += strideA;
+      gB += strideB;
+    }
+    wst = wst == ST - 1 ? 0 : wst + 1;
   };
-  const int nk = p.K / BKD;
-  issue(0, 0);
+
+  acc_t acc[TI][TJ];
+#pragma unroll
+  for (int a = 0; a < TI; ++a)
+#pragma unroll
+    for (int b = 0; b < TJ; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < ST - 1; ++i) issue();
+  int rst = 0;
   for (int kt = 0; kt < nk; ++kt) {
     // this wave's loads of k-tile kt have landed; the barrier makes every
-    // wave's visible and ends all reads of the other stage
-    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (kt + 1 < nk) issue(kt + 1, (kt + 1) & 1);
-    const double* st = lds + (kt & 1) * STAGE;
+    // wave's visible and ends all reads of the stage that is loaded next
+    __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 2) * LPS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __asm__ volatile("" ::: "memory");
+    issue();
+    const T* sA = lds + rst * STG;
+    const T* sB = sA + SA;
+    rst = rst == ST - 1 ? 0 : rst + 1;
+    T af[2][TI], bf[2][TJ];
+    FragA::read(af[0], sA, 0, wm * WTM, lane);
+    FragB::read(bf[0], sB, 0, wn * WTN, lane);
 #pragma unroll
-    for (int kk = 0; kk < BKD; kk += 4) {
-      const int k = kk + (lane >> 4);
-      double af[4], bf[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) af[a] = alpha * dma_frag<AT>(st, wm * 64 + a * 16 + (lane & 15), k);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int c = wn * 64 + b * 16 + (lane & 15);
-        bf[b] = dma_frag<!BT>(st + SA, c, k);
-        if constexpr (HAD) bf[b] *= dma_frag<!BT>(st + SA + SB, c, k);
+    for (int q = 0; q < BK / 4; ++q) {
+      if (q + 1 < BK / 4) {
+        FragA::read(af[(q + 1) & 1], sA, q + 1, wm * WTM, lane);
+        FragB::read(bf[(q + 1) & 1], sB, q + 1, wn * WTN, lane);
       }
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < TI; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = mfma4(af[a], bf[b], acc[a][b]);
+        for (int b = 0; b < TJ; ++b) acc[a][b] = mfma4(af[q & 1][a], bf[q & 1][b], acc[a][b]);
     }
   }
+  // no load into LDS may outlive the workgroup
+  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  if (local >= nfull) {
+    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    constexpr int SC1 = 16;  // cache policy: device-coherent
+    constexpr int W16 = 4 * (int)sizeof(T) / 16, TILE = BM * BN;
+    T* part = (T*)p.part + (size_t)(tile - nfull) * p.slices * TILE;
+    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(part + (size_t)slice * TILE), (short)0,
+                                                                  TILE * (int)sizeof(T), 0x00020000);
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < TI; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < TJ; ++b) {
+        struct Q { u4 v[W16]; };
+        const Q x = __builtin_bit_cast(Q, acc[a][b]);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm * 64 + a * 16 + dsub_row<double>(lane, r);
-        const int col = n0 + wn * 64 + b * 16 + (lane & 15);
-        if (row < p.M && col < p.N) {
-          const size_t off = (size_t)row * p.ldc + col;
-          gC[off] = acc[a][b][r];
-          if (p.C2) gC2[off] = acc[a][b][r];
+        for (int h = 0; h < W16; ++h)
+          __builtin_amdgcn_raw_buffer_store_b128(x.v[h], rs, (((a * TJ + b) * W16 + h) * NT + tid) * 16, 0, SC1);
+      }
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int* cnt = p.cnt + (tile - nfull);
+    if (tid == 0) {
+      last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.slices - 1;
+      if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last) return;
+#pragma unroll
+    for (int a = 0; a < TI; ++a)
+#pragma unroll
+      for (int b = 0; b < TJ; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
+    for (int z = 0; z < p.slices; ++z) {
+      rs = __builtin_amdgcn_make_buffer_rsrc((void*)(part + (size_t)z * TILE), (short)0, TILE * (int)sizeof(T),
+                                             0x00020000);
+#pragma unroll
+      for (int a = 0; a < TI; ++a)
+#pragma unroll
+        for (int b = 0; b < TJ; ++b) {
+          struct Q { u4 v[W16]; } x;
+#pragma unroll
+          for (int h = 0; h < W16; ++h)
+            x.v[h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (((a * TJ + b) * W16 + h) * NT + tid) * 16, 0, SC1);
+          acc[a][b] += __builtin_bit_cast(acc_t, x);
+        }
+    }
+  }
+
+  // C = alpha A B + beta C, its copy, and the Hadamard products that the
+  // next products of the sweep take as their operand
+  const gptr<T> gC = as_global(p.C), gC2 = as_global(p.C2);
+  const gptr<const T> gH1 = as_global(p.H1), gH2 = as_global(p.H2);
+  const gptr<T> gP1 = as_global(p.P1), gP2 = as_global(p.P2);
+  constexpr int FB = FragB::F;
+  typedef T vb __attribute__((ext_vector_type(FB)));
+#pragma unroll
+  for (int a = 0; a < TI; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm * WTM + FragA::row(a, dsub_row<T>(lane, r));
+      if (row >= p.M) continue;
+#pragma unroll
+      for (int b = 0; b < TJ; b += FB) {
+        const int col = n0 + wn * WTN + FragB::row(b, lane & 15);
+        const size_t off = (size_t)row * p.ldc + col;
+        vb v;
+#pragma unroll
+        for (int i = 0; i < FB; ++i) v[i] = p.alpha * acc[a][b + i][r];
+        if (FB > 1 && p.vec && col + FB <= p.N) {
+          if (p.beta != T(0)) v += p.beta * *(const gptr<const vb>)(gC + off);
+          *(gptr<vb>)(gC + off) = v;
+          if (p.C2) *(gptr<vb>)(gC2 + off) = v;
+          if (p.P1) *(gptr<vb>)(gP1 + off) = v * (p.H1 == p.C ? v : *(const gptr<const vb>)(gH1 + off));
+          if (p.P2) *(gptr<vb>)(gP2 + off) = v * (p.H2 == p.C ? v : *(const gptr<const vb>)(gH2 + off));
+        } else {
+#pragma unroll
+          for (int i = 0; i < FB; ++i) {
+            if (col + i >= p.N) continue;
+            const size_t o = off + i;
+            T x = v[i];
+            if (p.beta != T(0)) x += p.beta * gC[o];
+            gC[o] = x;
+            if (p.C2) gC2[o] = x;
+            if (p.P1) gP1[o] = x * (p.H1 == p.C ? x : gH1[o]);
+            if (p.P2) gP2[o] = x * (p.H2 == p.C ? x : gH2[o]);
+          }
         }
       }
+    }
+#endif
 }
 
-template <bool AT, bool BT, bool HAD>
-__global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs<double> p) {
-  gemm_dma_body<AT, BT, HAD>(p, blockIdx.x, gridDim.x);
+template <typename T, typename C, bool AT, bool BT>
+__global__ __launch_bounds__(64 * C::WM * C::WN, C::WPE) void gemm_tile_kernel(GemmArgs<T> p) {
+  gemm_tile_body<T, C, AT, BT>(p, blockIdx.x);
 }
-template <bool AT, bool BT, bool HAD>
-__global__ __launch_bounds__(256) void gemm_dma_group_kernel(const GemmArgs<double>* tab, const int* offs,
-                                                              int nprob) {
+// Grouped form: workgroup -> (problem, local unit) through the prefix sums.
+template <typename T, typename C, bool AT, bool BT>
+__global__ __launch_bounds__(64 * C::WM * C::WN, C::WPE) void gemm_tile_group_kernel(const GemmArgs<T>* tab,
+                                                                                      const int* offs, int nprob) {
   int pid = 0;
   while (pid + 1 < nprob && (int)blockIdx.x >= offs[pid + 1]) ++pid;
-  const GemmArgs<double> p = tab[pid];
-  gemm_dma_body<AT, BT, HAD>(p, blockIdx.x - offs[pid], offs[pid + 1] - offs[pid]);
+  const GemmArgs<T> p = tab[pid];
+  gemm_tile_body<T, C, AT, BT>(p, blockIdx.x - offs[pid]);
 }
 
 template <typename T>
-bool gemm_dma_ok(const GemmArgs<T>& g, bool had) {
-  if (sizeof(T) != 8 || g.K <= 0 || g.M <= 0 || g.N <= 0) return false;
+bool gemm_tile_ok(const GemmArgs<T>& g, bool a_t, bool b_t) {
+  constexpr int V = Chunk<T>::V;
   auto al16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
-  return g.beta == T(0) && !g.lower && g.K % (had ? 8 : 16) == 0 && g.lda % 2 == 0 && g.ldb % 2 == 0 &&
-         al16(g.A) && al16(g.B1) && (!had || al16(g.B2));
+  // 32-bit offsets inside a tile, and whole 16-byte chunks along the
+  // contiguous index: along k, K itself; along the rows, the row length
+  // (the last chunk of a row may reach past M or N, not past lda or ldb)
+  const long span = 128L * (g.lda > g.ldb ? g.lda : g.ldb) * (long)sizeof(T);
+  return g.M > 0 && g.N > 0 && g.K > 0 && !g.B2 && g.lda % V == 0 && g.ldb % V == 0 && span < (1L << 31) &&
+         (a_t ? (g.M + V - 1) / V * V <= g.lda : g.K % V == 0) &&
+         (b_t ? g.K % V == 0 : (g.N + V - 1) / V * V <= g.ldb) && al16(g.A) && al16(g.B1);
 }
-template bool gemm_dma_ok<double>(const GemmArgs<double>&, bool);
-template bool gemm_dma_ok<float>(const GemmArgs<float>&, bool);
+template bool gemm_tile_ok<double>(const GemmArgs<double>&, bool, bool);
+template bool gemm_tile_ok<float>(const GemmArgs<float>&, bool, bool);
 
-static void launch_dma(hipStream_t s, const GemmArgs<double>& a, bool at, bool bt, bool had) {
-  dim3 grid(gemm_tile_count(a.M, a.N, DM)), block(256);
-#define THCCP_DMA_CASE(AT_, BT_, HAD_)                                                   \
-  if (at == AT_ && bt == BT_ && had == HAD_) {                                           \
-    hipLaunchKernelGGL((gemm_dma_kernel<AT_, BT_, HAD_>), grid, block, 0, s, a);         \
-    return;                                                                              \
-  }
-  THCCP_DMA_CASE(false, false, false)
-  THCCP_DMA_CASE(true, false, false)
-  THCCP_DMA_CASE(false, false, true)
-  THCCP_DMA_CASE(true, false, true)
-  THCCP_DMA_CASE(false, true, false)
-  THCCP_DMA_CASE(true, true, false)
-#undef THCCP_DMA_CASE
+template <typename T>
+void gemm_set_vec(GemmArgs<T>& g) {
+  const uintptr_t all = (uintptr_t)g.C | (uintptr_t)g.C2 | (uintptr_t)g.H1 | (uintptr_t)g.P1 | (uintptr_t)g.H2 |
+                        (uintptr_t)g.P2;
+  g.vec = (all & 15) == 0 && g.ldc % Chunk<T>::V == 0;
 }
-static void launch_dma_group(hipStream_t s, const GemmArgs<double>* tab, const int* offs, int nprob, int tiles,
-                             bool at, bool bt, bool had) {
-  dim3 grid(tiles), block(256);
-#define THCCP_DMA_GCASE(AT_, BT_, HAD_)                                                               \
-  if (at == AT_ && bt == BT_ && had == HAD_) {                                                        \
-    hipLaunchKernelGGL((gemm_dma_group_kernel<AT_, BT_, HAD_>), grid, block, 0, s, tab, offs, nprob); \
-    return;                                                                                           \
+template void gemm_set_vec<double>(GemmArgs<double>&);
+template void gemm_set_vec<float>(GemmArgs<float>&);
+
+// Units (workgroups) of g in tile form bm.
+template <typename T>
+int gemm_units(const GemmArgs<T>& g, int bm) {
+  const int t = gemm_tile_count(g.M, g.N, bm, g.lower);
+  return g.slices > 1 ? g.nfull + (t - g.nfull) * g.slices : t;
+}
+template int gemm_units<double>(const GemmArgs<double>&, int);
+template int gemm_units<float>(const GemmArgs<float>&, int);
+
+// K slices of one product, from its own shape alone (a problem gives the
+// same bits alone and in any group).
+//   - At least 256 tiles of 64: the tiles past a whole number per compute
+//     unit are split, so that the last round is shared by all units
+//     (800 x 4000 x 4000: 819 = 3 x 256 + 51 tiles, 51 x 5 slices).
+//   - Fewer: all of its tiles, into as many slices of at least 128 k as
+//     give 256 workgroups of 32 x 32 tiles (100 x 400 x 500: 52 tiles).
+// FP64 only: the sums of an FP32 plan keep the one order of k, since its
+// factors would follow another order's rounding by some 1e-6.
+template <typename T>
+void gemm_plan_slices(GemmArgs<T>& g) {
+  const int t64 = gemm_tile_count(g.M, g.N, 64, g.lower);
+  g.slices = 1;
+  g.nfull = 0;
+  if (sizeof(T) == 4) return;
+  if (t64 >= 256) {
+    const int rest = t64 % 256;
+    if (!rest) return;
+    int s = 256 / rest;
+    s = s < g.K / 256 ? s : g.K / 256;
+    if (s > 8) s = 8;
+    if (s < 2) return;
+    g.nfull = t64 - rest;
+    g.slices = s;
+    return;
   }
-  THCCP_DMA_GCASE(false, false, false)
-  THCCP_DMA_GCASE(true, false, false)
-  THCCP_DMA_GCASE(false, false, true)
-  THCCP_DMA_GCASE(true, false, true)
-  THCCP_DMA_GCASE(false, true, false)
-#undef THCCP_DMA_GCASE
+  const int t32 = gemm_tile_count(g.M, g.N, 32, g.lower);
+  int s = 256 / t32;
+  s = s < g.K / 128 ? s : g.K / 128;
+  if (s > 8) s = 8;
+  if (s >= 2) g.slices = s;
+}
+template void gemm_plan_slices<double>(GemmArgs<double>&);
+template void gemm_plan_slices<float>(GemmArgs<float>&);
+
+// Tile form of a launch.  A split product with unsplit tiles runs in the
+// form its split is made for (64); otherwise the largest form that gives
+// every compute unit work:
+//   - 32 below 256 tiles of 64 (a 64-tile alone on its unit waits for its
+//     loads; 500 x 400 x 500: 22 us against 10.5 us);
+//   - 128 where two full rounds of it exist and its last round wastes less
+//     than its higher rate gives (4000 x 4000: 1024 tiles of 128 are four
+//     for each unit, 66.5 against 62 TFLOP/s; 1920 x 15360: 1800 are eight
+//     for some units, 62 against 64).
+template <typename T>
+int gemm_tile_form(const std::vector<GemmArgs<T>>& v) {
+  long t64 = 0, t128 = 0;
+  bool tail = false, split = false;
+  for (auto& g : v) {
+    t64 += gemm_tile_count(g.M, g.N, 64, g.lower);
+    t128 += gemm_tile_count(g.M, g.N, 128, g.lower);
+    split = split || g.slices > 1;
+    tail = tail || (g.slices > 1 && g.nfull > 0);
+  }
+  if (t64 < 256) return 32;
+  if (tail || split || t128 < 512) return 64;
+  return 4.0 * ((t128 + 255) / 256) / 1.06 < (double)((t64 + 255) / 256) ? 128 : 64;
+}
+template int gemm_tile_form<double>(const std::vector<GemmArgs<double>>&);
+template int gemm_tile_form<float>(const std::vector<GemmArgs<float>>&);
+
+template <typename T, typename C>
+static void launch_tile_group(hipStream_t s, const GemmArgs<T>* tab, const int* offs, int nprob, int units, bool at,
+                              bool bt) {
+  const dim3 grid(units), block(64 * C::WM * C::WN);
+  if (at && !bt) hipLaunchKernelGGL((gemm_tile_group_kernel<T, C, true, false>), grid, block, 0, s, tab, offs, nprob);
+  else if (!at && !bt)
+    hipLaunchKernelGGL((gemm_tile_group_kernel<T, C, false, false>), grid, block, 0, s, tab, offs, nprob);
+  else hipLaunchKernelGGL((gemm_tile_group_kernel<T, C, false, true>), grid, block, 0, s, tab, offs, nprob);
 }
 
-template <typename T, int BM, int BN>
-static void launch_tile(hipStream_t s, const GemmArgs<T>& a, bool at, bool bt, bool had) {
-  const int tiles = BM == BN ? gemm_tile_count(a.M, a.N, BM, a.lower) : ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  dim3 grid(tiles), block(256);
-#define THCCP_GEMM_CASE(AT_, BT_, HAD_)                                           \
-  if (at == AT_ && bt == BT_ && had == HAD_) {                                    \
-    hipLaunchKernelGGL((gemm_kernel<T, BM, BN, AT_, BT_, HAD_>), grid, block, 0, s, a); \
-    return;                                                                       \
+template <typename T>
+void gemm_group(hipStream_t s, const GemmArgs<T>* tab, const int* offs, int nprob, int units, bool a_t, bool b_t,
+                int bm) {
+  if (units <= 0) return;
+  if (bm == 128) launch_tile_group<T, TileBig>(s, tab, offs, nprob, units, a_t, b_t);
+  else if (bm == 64) launch_tile_group<T, TileMid>(s, tab, offs, nprob, units, a_t, b_t);
+  else launch_tile_group<T, TileSmall>(s, tab, offs, nprob, units, a_t, b_t);
+}
+template void gemm_group<double>(hipStream_t, const GemmArgs<double>*, const int*, int, int, bool, bool, int);
+template void gemm_group<float>(hipStream_t, const GemmArgs<float>*, const int*, int, int, bool, bool, int);
+
+template <typename T, typename C>
+static void launch_tile_single(hipStream_t s, const GemmArgs<T>& a, bool at, bool bt) {
+  const dim3 grid(gemm_units(a, C::BM)), block(64 * C::WM * C::WN);
+  if (at && bt) hipLaunchKernelGGL((gemm_tile_kernel<T, C, true, true>), grid, block, 0, s, a);
+  else if (at) hipLaunchKernelGGL((gemm_tile_kernel<T, C, true, false>), grid, block, 0, s, a);
+  else if (bt) hipLaunchKernelGGL((gemm_tile_kernel<T, C, false, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemm_tile_kernel<T, C, false, false>), grid, block, 0, s, a);
+}
+
+template <typename T>
+static void launch_staged(hipStream_t s, const GemmArgs<T>& a, bool at, bool bt, bool had) {
+  const dim3 grid(gemm_tile_count(a.M, a.N, 64, a.lower)), block(256);
+#define THCCP_GEMM_CASE(AT_, BT_, HAD_)                                                 \
+  if (at == AT_ && bt == BT_ && had == HAD_) {                                          \
+    hipLaunchKernelGGL((gemm_kernel<T, 64, 64, AT_, BT_, HAD_>), grid, block, 0, s, a); \
+    return;                                                                             \
   }
   THCCP_GEMM_CASE(false, false, false)
   THCCP_GEMM_CASE(true, false, false)
@@ -403,72 +681,28 @@ static void launch_tile(hipStream_t s, const GemmArgs<T>& a, bool at, bool bt, b
 #undef THCCP_GEMM_CASE
 }
 
-int gemm_default_tile(int M, int N) {
-  // 64 x 64 tiles (three workgroups per compute unit) unless there are
-  // thousands of 128 x 128 tiles
-  const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-  return t128 >= 4096 ? 128 : 64;
-}
-
 template <typename T>
-static void gemm_dispatch(hipStream_t s, const GemmArgs<T>& a, bool at, bool bt, bool had) {
+static void gemm_dispatch(hipStream_t s, GemmArgs<T> a, bool at, bool bt) {
   if (a.M <= 0 || a.N <= 0) return;
-  if constexpr (sizeof(T) == 8) {
-    // the direct-load 128-tile path wherever its requirements hold
-    if (!(had && bt) && gemm_dma_ok(a, had)) {
-      launch_dma(s, a, at, bt, had);
-      return;
-    }
+  if (!gemm_tile_ok(a, at, bt)) {
+    launch_staged<T>(s, a, at, bt, a.B2 != nullptr);
+    return;
   }
-  if (gemm_default_tile(a.M, a.N) == 128) launch_tile<T, 128, 128>(s, a, at, bt, had);
-  else launch_tile<T, 64, 64>(s, a, at, bt, had);
+  gemm_set_vec(a);
+  const int bm = gemm_tile_form<T>({a});
+  if (bm == 128) launch_tile_single<T, TileBig>(s, a, at, bt);
+  else if (bm == 64) launch_tile_single<T, TileMid>(s, a, at, bt);
+  else launch_tile_single<T, TileSmall>(s, a, at, bt);
 }
-
-template <typename T, int BM>
-static void launch_group_tile(hipStream_t s, const GemmArgs<T>* tab, const int* offs, int nprob, int tiles,
-                              bool at, bool bt, bool had) {
-  dim3 grid(tiles), block(256);
-#define THCCP_GEMM_GCASE(AT_, BT_, HAD_)                                                              \
-  if (at == AT_ && bt == BT_ && had == HAD_) {                                                       \
-    hipLaunchKernelGGL((gemm_group_kernel<T, BM, BM, AT_, BT_, HAD_>), grid, block, 0, s, tab, offs, nprob); \
-    return;                                                                                          \
-  }
-  THCCP_GEMM_GCASE(false, false, false)
-  THCCP_GEMM_GCASE(true, false, false)
-  THCCP_GEMM_GCASE(false, false, true)
-  THCCP_GEMM_GCASE(true, false, true)
-  THCCP_GEMM_GCASE(false, true, false)
-#undef THCCP_GEMM_GCASE
-}
-
-template <typename T>
-void gemm_group(hipStream_t s, const GemmArgs<T>* tab, const int* offs, int nprob, int total_tiles, bool a_t,
-                bool b_t, bool had, int bm) {
-  if (total_tiles <= 0) return;
-  if constexpr (sizeof(T) == 8) {
-    // FP64: bm = 128 is the direct-load path (the caller checked gemm_dma_ok
-    // for every entry)
-    if (bm == 128) {
-      launch_dma_group(s, (const GemmArgs<double>*)tab, offs, nprob, total_tiles, a_t, b_t, had);
-      return;
-    }
-  }
-  if (bm == 128) launch_group_tile<T, 128>(s, tab, offs, nprob, total_tiles, a_t, b_t, had);
-  else launch_group_tile<T, 64>(s, tab, offs, nprob, total_tiles, a_t, b_t, had);
-}
-template void gemm_group<double>(hipStream_t, const GemmArgs<double>*, const int*, int, int, bool, bool, bool, int);
-template void gemm_group<float>(hipStream_t, const GemmArgs<float>*, const int*, int, int, bool, bool, bool, int);
 
 void gemm_f64(hipStream_t s, const GemmF64& g) {
-  GemmArgs<double> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2,
-                     g.alpha, g.beta, g.done, nullptr, 0, 0};
-  gemm_dispatch<double>(s, a, g.a_t, g.b_t, g.B2 != nullptr);
+  GemmArgs<double> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
+  gemm_dispatch<double>(s, a, g.a_t, g.b_t);
 }
 
 void gemm_f32(hipStream_t s, const GemmF32& g) {
-  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2,
-                    g.alpha, g.beta, g.done, nullptr, 0, 0};
-  gemm_dispatch<float>(s, a, g.a_t, g.b_t, g.B2 != nullptr);
+  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
+  gemm_dispatch<float>(s, a, g.a_t, g.b_t);
 }
 
 }  // namespace thccp

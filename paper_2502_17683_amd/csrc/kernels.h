@@ -20,8 +20,7 @@ namespace thccp {
 // C[M x N] = alpha * op(A)[M x K] * op(B)[K x N] + beta * C, row-major C.
 //   a_t = false: A[i*lda + k];  a_t = true: A[k*lda + i]   (A stored K x M)
 //   b_t = false: B[k*ldb + j];  b_t = true: B[j*ldb + k]   (B stored N x K)
-//   B2 != nullptr: every B element is B1[.] * B2[.] (Hadamard product fused
-//   into the operand load; same layout and leading dimension).
+//   B2 != nullptr: every B element is B1[.] * B2[.] (single products only).
 //   C2 != nullptr: the result is also written to C2 (same ldc).
 //   done != nullptr: the problem is skipped once *done is set.
 //   gate != nullptr: the problem is skipped unless *gate == want (per-problem
@@ -29,6 +28,12 @@ namespace thccp {
 //   lower != 0: tiles strictly above the diagonal are skipped (C is only
 //   needed on and below it, as in a symmetric rank-k update); for square
 //   C only the lower tiles are launched (see gemm_tile_count).
+//   P1 != nullptr: P1 = C o H1 as well (ldc; H1 == C: the square), P2
+//   likewise with H2: the pair operand of a later product, formed while C
+//   is in registers.
+//   slices > 1: tiles at or past nfull are split over K (gemm_plan_slices);
+//   part: their partial tiles, cnt: one zeroed counter each.
+//   vec: C, C2, H and P take 16-byte accesses.
 template <typename T>
 struct GemmArgs {
   int M, N, K;
@@ -40,6 +45,12 @@ struct GemmArgs {
   const int32_t* gate = nullptr;
   int32_t want = 0;
   int32_t lower = 0;
+  const T* H1 = nullptr; T* P1 = nullptr;
+  const T* H2 = nullptr; T* P2 = nullptr;
+  int32_t nfull = 0, slices = 1;
+  void* part = nullptr;
+  int32_t* cnt = nullptr;
+  int32_t vec = 0;
 };
 struct GemmF64 {
   int M, N, K;
@@ -59,27 +70,44 @@ struct GemmF32 {
 };
 void gemm_f64(hipStream_t s, const GemmF64& g);
 void gemm_f32(hipStream_t s, const GemmF32& g);
-// Tile edge the heuristic picks (64; 128 only for thousands of 128-tiles).
-int gemm_default_tile(int M, int N);
 // Tiles of one GEMM; a lower-triangle GEMM (lower != 0, square) launches
 // only the T (T + 1) / 2 tiles on and below the diagonal.
 inline int gemm_tile_count(int M, int N, int bm, int lower = 0) {
   const int tm = (M + bm - 1) / bm, tn = (N + bm - 1) / bm;
   return lower && M == N ? tm * (tm + 1) / 2 : tm * tn;
 }
-// Whether the FP64 direct-load 128-tile path can take this product: beta =
-// 0, not lower-triangle, K a multiple of its k-step (8 with a Hadamard pair,
-// 16 otherwise), even leading dimensions, 16-byte aligned operands (always
-// false for FP32).
+// First k of slice z of `slices` (multiples of 32, so that every tile form
+// cuts K at the same places).
+__host__ __device__ inline int gemm_slice_k(int K, int slices, int z) {
+  const long b = (K + 31) / 32;
+  const int k = (int)(b * z / slices) * 32;
+  return k < K ? k : K;
+}
+// Whether the direct-load tiles can take this product: 16-byte aligned
+// operands whose leading dimensions, and K where an operand is contiguous
+// along k, are multiples of a 16-byte chunk.
 template <typename T>
-bool gemm_dma_ok(const GemmArgs<T>& g, bool had);
-// Grouped launch: tab[nprob] problems with identical (a_t, b_t, Hadamard)
-// flags, tile edge bm (64 or 128; for FP64, 128 is the direct-load path and
-// every entry must pass gemm_dma_ok), offs[nprob + 1] prefix sums of
-// gemm_tile_count(M_p, N_p, bm).
+bool gemm_tile_ok(const GemmArgs<T>& g, bool a_t, bool b_t);
+// Chooses nfull and slices of a product of a plan (part and cnt are the
+// caller's: (tiles - nfull) slices bm^2 elements and tiles - nfull zeroed
+// counters).
 template <typename T>
-void gemm_group(hipStream_t s, const GemmArgs<T>* tab, const int* offs, int nprob, int total_tiles, bool a_t,
-                bool b_t, bool had, int bm);
+void gemm_plan_slices(GemmArgs<T>& g);
+// Workgroups of a product in tile form bm.
+template <typename T>
+int gemm_units(const GemmArgs<T>& g, int bm);
+// Tile form (32, 64 or 128) of a grouped launch.
+template <typename T>
+int gemm_tile_form(const std::vector<GemmArgs<T>>& v);
+// Grouped launch: tab[nprob] products with identical (a_t, b_t) flags, all
+// of them gemm_tile_ok, in tile form bm; offs[nprob + 1] prefix sums of
+// gemm_units.
+template <typename T>
+void gemm_group(hipStream_t s, const GemmArgs<T>* tab, const int* offs, int nprob, int units, bool a_t, bool b_t,
+                int bm);
+// Whether C and its companions take 16-byte accesses (sets g.vec).
+template <typename T>
+void gemm_set_vec(GemmArgs<T>& g);
 
 // -------------------------------------------------- Cholesky / triangular solve
 // One problem of the blocked factorisation and row solves.  V: Tp x Tp
@@ -262,6 +290,10 @@ void hadamard_inplace_f64(hipStream_t s, double* A, const double* B, size_t coun
 void transposed_dot_f64(hipStream_t s, const double* P, const double* Q, int R, int ld, double* partials,
                         double* out);
 void fill_bytes(hipStream_t s, void* p, size_t bytes);
+template <typename T>
+void hadamard(hipStream_t s, const T* a, const T* b, T* out, size_t count);
+template <typename T>
+void copy_rows_f64(hipStream_t s, const double* src, int rows, int cols, T* dst, int ld);
 void state_reset(hipStream_t s, DevState* st, double* norm2_src, double fit_target);
 void cast_f64_to_f32(hipStream_t s, const double* a, float* b, size_t count);
 void copy_normalised_init(hipStream_t s, const double* src, int n, int R, int ld, double* dst);

@@ -445,6 +445,38 @@ void hadamard_inplace_f64(hipStream_t s, double* A, const double* B, size_t coun
   hipLaunchKernelGGL(hadamard_inplace_kernel, dim3(grid), dim3(256), 0, s, A, B, count);
 }
 
+// out = a o b.
+template <typename T>
+__global__ void hadamard_kernel(const T* a, const T* b, T* out, size_t count) {
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (size_t)gridDim.x * 256)
+    out[e] = a[e] * b[e];
+}
+template <typename T>
+void hadamard(hipStream_t s, const T* a, const T* b, T* out, size_t count) {
+  size_t grid = (count + 255) / 256;
+  if (grid > 8192) grid = 8192;
+  if (grid < 1) grid = 1;
+  hipLaunchKernelGGL((hadamard_kernel<T>), dim3((unsigned)grid), dim3(256), 0, s, a, b, out, count);
+}
+template void hadamard<double>(hipStream_t, const double*, const double*, double*, size_t);
+template void hadamard<float>(hipStream_t, const float*, const float*, float*, size_t);
+
+// dst (rows x cols, ld) = src (rows x cols, dense), rounded to T.
+template <typename T>
+__global__ void copy_rows_kernel(const double* src, int rows, int cols, T* dst, int ld) {
+  const size_t total = (size_t)rows * cols;
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256)
+    dst[e / cols * ld + e % cols] = (T)src[e];
+}
+template <typename T>
+void copy_rows_f64(hipStream_t s, const double* src, int rows, int cols, T* dst, int ld) {
+  size_t grid = ((size_t)rows * cols + 255) / 256;
+  if (grid > 8192) grid = 8192;
+  hipLaunchKernelGGL((copy_rows_kernel<T>), dim3((unsigned)grid), dim3(256), 0, s, src, rows, cols, dst, ld);
+}
+template void copy_rows_f64<double>(hipStream_t, const double*, int, int, double*, int);
+template void copy_rows_f64<float>(hipStream_t, const double*, int, int, float*, int);
+
 // sum_ij P[j][i] Q[i][j] over R x R (ld): 64x64 tiles through LDS, one
 // partial per tile, then a fixed-order final sum.
 __global__ __launch_bounds__(256) void tdot_tiles_kernel(const double* P, const double* Q, int R, int ld,

@@ -198,7 +198,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs<T> p) {
 // lane past the end of K reads an offset outside the buffer's bound, which
 // writes zeros, so K needs no multiple of the k-step.  Rows past the edge
 // read a clamped in-range address and feed only elements that are not
-// stored.
+// stored.  (The compiler waits for the new loads before the reads of the
+// present stage; global_load_lds with the zeros from a branch does not, and
+// measured the same or 2% slower: the other workgroups of the unit cover
+// the wait.)
 //
 // What bounds it: the FP64 matrix instruction takes 64 cycles, so 16 of
 // them (a 64 x 64 wave tile and 4 of k) leave ~1000 cycles for a few LDS
@@ -256,6 +259,9 @@ struct TileMid {    // 64 x 64, four waves of 32 x 32, four or five workgroups p
 struct TileSmall {  // 32 x 32, four waves of 16 x 16, long k-steps, four stages
   static constexpr int BM = 32, BN = 32, WM = 2, WN = 2, BKB = 256, ST = 4, WPE = 2;
 };
+struct TileLong {   // 32 x 32 with twice the k-step: few tiles, long K, both operands contiguous along their rows
+  static constexpr int BM = 32, BN = 32, WM = 2, WN = 2, BKB = 512, ST = 2, WPE = 2;
+};
 
 // Chunk c of row r of a k-contiguous operand lies in slot c ^ chunk_swizzle(r)
 // of the row (8 or 16 chunks: half or the whole of the 64 banks).
@@ -278,7 +284,7 @@ struct OperandLoad {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = i * NT + tid;
-      if (KC) {
+      if constexpr (KC) {
         const int r = c / KP, kp = (c % KP) ^ chunk_swizzle<KP>(r);
         off[i] = (uint32_t)(((size_t)(min(r0 + r, rows - 1) - r0) * ld + kp * V) * sizeof(T));
         kof[i] = kp * V;
@@ -289,7 +295,7 @@ struct OperandLoad {
       }
     }
   }
-  // base: the operand at (r0, k0); left: the k's from k0 on (none: zeros)
+  // base: the operand at (r0, k0); left: the k's from k0 on (past them: zeros)
   __device__ __forceinline__ void issue(const T* base, int left, T* stage, int w) const {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7ffffff0, 0x00020000);
 #pragma unroll
@@ -329,7 +335,7 @@ struct OperandFrag {
 };
 
 template <typename T, typename C, bool AT, bool BT>
-__device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local) {
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local, T* lds, int& last) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int BM = C::BM, BN = C::BN, ST = C::ST, NT = 64 * C::WM * C::WN, V = Chunk<T>::V;
   constexpr int BK = C::BKB / (int)sizeof(T);
@@ -341,9 +347,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local) 
   typedef OperandFrag<T, BM, BK, !AT, TI> FragA;
   typedef OperandFrag<T, BN, BK, BT, TJ> FragB;
   constexpr int LPS = LoadA::PER + LoadB::PER;  // loads of a wave per stage
-  __shared__ __attribute__((aligned(1024))) T lds[ST * STG];
-  __shared__ int last;
-
+  // fragments held: of the present 4 of k and of the next D - 1, so that a
+  // read has some 200 cycles of products to return in
+  constexpr int D = TI * TJ >= 4 ? 2 : BK / 4 < 8 ? BK / 4 : 8;
   if (p.done && *p.done) return;
   if (p.gate && *p.gate != p.want) return;
   const int tiles_n = (p.N + BN - 1) / BN, tiles_m = (p.M + BM - 1) / BM;
@@ -418,19 +424,24 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local) 
     const T* sA = lds + rst * STG;
     const T* sB = sA + SA;
     rst = rst == ST - 1 ? 0 : rst + 1;
-    T af[2][TI], bf[2][TJ];
-    FragA::read(af[0], sA, 0, wm * WTM, lane);
-    FragB::read(bf[0], sB, 0, wn * WTN, lane);
+    T af[D][TI], bf[D][TJ];
+#pragma unroll
+    for (int q = 0; q < D - 1; ++q) {
+      FragA::read(af[q], sA, q, wm * WTM, lane);
+      FragB::read(bf[q], sB, q, wn * WTN, lane);
+    }
 #pragma unroll
     for (int q = 0; q < BK / 4; ++q) {
-      if (q + 1 < BK / 4) {
-        FragA::read(af[(q + 1) & 1], sA, q + 1, wm * WTM, lane);
-        FragB::read(bf[(q + 1) & 1], sB, q + 1, wn * WTN, lane);
+      if (q + D - 1 < BK / 4) {
+        FragA::read(af[(q + D - 1) % D], sA, q + D - 1, wm * WTM, lane);
+        FragB::read(bf[(q + D - 1) % D], sB, q + D - 1, wn * WTN, lane);
       }
+      if (D > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int a = 0; a < TI; ++a)
 #pragma unroll
-        for (int b = 0; b < TJ; ++b) acc[a][b] = mfma4(af[q & 1][a], bf[q & 1][b], acc[a][b]);
+        for (int b = 0; b < TJ; ++b) acc[a][b] = mfma4(af[q % D][a], bf[q % D][b], acc[a][b]);
+      if (D > 2) __builtin_amdgcn_sched_barrier(0);
     }
   }
   // no load into LDS may outlive the workgroup
@@ -526,18 +537,42 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local) 
 #endif
 }
 
+// Bytes of LDS of a tile form.
+template <typename C>
+constexpr int tile_lds() {
+  return C::ST * (C::BM + C::BN) * C::BKB;
+}
+
 template <typename T, typename C, bool AT, bool BT>
 __global__ __launch_bounds__(64 * C::WM * C::WN, C::WPE) void gemm_tile_kernel(GemmArgs<T> p) {
-  gemm_tile_body<T, C, AT, BT>(p, blockIdx.x);
+  __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+  __shared__ int last;
+  gemm_tile_body<T, C, AT, BT>(p, blockIdx.x, (T*)lds, last);
+}
+// Two independent products in one launch: workgroups below n1 take p (form
+// C1, op(A) = A^T), the others q (form C2, op(B) = B^T).
+template <typename T, typename C1, typename C2>
+__global__ __launch_bounds__(256, 2) void gemm_tile_two_kernel(GemmArgs<T> p, GemmArgs<T> q, int n1) {
+  static_assert(C1::WM * C1::WN == 4 && C2::WM * C2::WN == 4, "256 threads");
+  __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C1>() > tile_lds<C2>() ? tile_lds<C1>() : tile_lds<C2>()];
+  __shared__ int last;
+  if ((int)blockIdx.x < n1) {
+    __builtin_amdgcn_s_setprio(3);  // the launch ends with these
+    gemm_tile_body<T, C1, true, false>(p, blockIdx.x, (T*)lds, last);
+  } else {
+    gemm_tile_body<T, C2, false, true>(q, blockIdx.x - n1, (T*)lds, last);
+  }
 }
 // Grouped form: workgroup -> (problem, local unit) through the prefix sums.
 template <typename T, typename C, bool AT, bool BT>
 __global__ __launch_bounds__(64 * C::WM * C::WN, C::WPE) void gemm_tile_group_kernel(const GemmArgs<T>* tab,
                                                                                       const int* offs, int nprob) {
+  __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+  __shared__ int last;
   int pid = 0;
   while (pid + 1 < nprob && (int)blockIdx.x >= offs[pid + 1]) ++pid;
   const GemmArgs<T> p = tab[pid];
-  gemm_tile_body<T, C, AT, BT>(p, blockIdx.x - offs[pid]);
+  gemm_tile_body<T, C, AT, BT>(p, blockIdx.x - offs[pid], (T*)lds, last);
 }
 
 template <typename T>
@@ -698,6 +733,25 @@ static void gemm_dispatch(hipStream_t s, GemmArgs<T> a, bool at, bool bt) {
 void gemm_f64(hipStream_t s, const GemmF64& g) {
   GemmArgs<double> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
   gemm_dispatch<double>(s, a, g.a_t, g.b_t);
+}
+
+// dW = A^T B (M x N, few tiles, long K) and dX = C D^T.  The 16 x 16 tiles
+// of dW are chains of K / 4 dependent products (their order of K is kept),
+// so only 64 workgroups run; at 256 x 256 x 8192 that is 64 us with the
+// LDS reads eight products ahead (84 us one product ahead), beside the other
+// product (17 us alone at 8192 x 256 x 256) 78 us.
+void gemm_f32_two(hipStream_t s, const GemmF32& g, const GemmF32& h) {
+  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
+  GemmArgs<float> b{h.M, h.N, h.K, h.A, h.lda, h.B1, h.B2, h.ldb, h.C, h.ldc, h.C2, h.alpha, h.beta, h.done};
+  if (!g.a_t || g.b_t || h.a_t || !h.b_t || !gemm_tile_ok(a, true, false) || !gemm_tile_ok(b, false, true)) {
+    gemm_f32(s, g);
+    gemm_f32(s, h);
+    return;
+  }
+  gemm_set_vec(a);
+  gemm_set_vec(b);
+  const int n1 = gemm_units(a, TileLong::BM), n2 = gemm_units(b, TileMid::BM);
+  hipLaunchKernelGGL((gemm_tile_two_kernel<float, TileLong, TileMid>), dim3(n1 + n2), dim3(256), 0, s, a, b, n1);
 }
 
 void gemm_f32(hipStream_t s, const GemmF32& g) {

@@ -70,6 +70,9 @@ struct GemmF32 {
 };
 void gemm_f64(hipStream_t s, const GemmF64& g);
 void gemm_f32(hipStream_t s, const GemmF32& g);
+// Two independent products, op(A) = A^T of the first and op(B) = B^T of the
+// second, side by side where their shapes allow it.
+void gemm_f32_two(hipStream_t s, const GemmF32& g, const GemmF32& h);
 // Tiles of one GEMM; a lower-triangle GEMM (lower != 0, square) launches
 // only the T (T + 1) / 2 tiles on and below the diagonal.
 inline int gemm_tile_count(int M, int N, int bm, int lower = 0) {

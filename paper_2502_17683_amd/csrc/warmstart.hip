@@ -60,6 +60,14 @@ constexpr size_t PK_W2T_BYTES = ((size_t)(PK_B3 + D_OUT) * 4 + 255) & ~(size_t)2
 constexpr size_t PK_BYTES = PK_W2T_BYTES + (size_t)WIDTH * WIDTH * 2;
 
 constexpr int CHUNK = 256;  // rows per partial sum of the reductions over rows
+constexpr int CG = 32;      // columns per workgroup of the gradients' reductions
+// Partial gradients of the small blocks, one vector per CHUNK rows.
+constexpr int PG_W1 = 0;
+constexpr int PG_B1 = PG_W1 + D_IN * WIDTH;
+constexpr int PG_B2 = PG_B1 + WIDTH;
+constexpr int PG_W3 = PG_B2 + WIDTH;
+constexpr int PG_B3 = PG_W3 + WIDTH * D_OUT;
+constexpr int PG_LEN = PG_B3 + D_OUT;
 constexpr double TINY = 1e-300;
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -383,35 +391,53 @@ __global__ void zero_f32(float* a, size_t n) {
 }
 
 // ------------------------------------------------------------ network, FP32
-__global__ __launch_bounds__(256) void l1_fwd_kernel(const float* prm, const float* x, const int* idx, int rows,
-                                                     float* a1, float* h1) {
-  const int r = blockIdx.x, j = threadIdx.x;
-  const int src = idx ? idx[r] : r;
-  float a = prm[OFF_B1 + j];
+// The training step runs in eleven launches.  What bounded the first form of
+// it were its reductions over the rows: one workgroup per 256 rows and one
+// load at a time (192 us each at 8192 rows, three of them).  Now a row's
+// values are formed by many threads into LDS, and one thread per output
+// adds them from there; the element-wise passes ride along, and a1 and h2
+// are formed again where they are needed (8 products and one sigmoid)
+// instead of stored.  Every sum keeps its order (rows of a chunk one by
+// one, then the chunks): training is a long recursion, so another order
+// would end in other weights.
+__device__ __forceinline__ float layer1(const float w[D_IN], float b, const float* x) {
+  float a = b;
 #pragma unroll
-  for (int i = 0; i < D_IN; ++i) a += x[(size_t)src * D_IN + i] * prm[OFF_W1 + i * WIDTH + j];
-  a1[(size_t)r * WIDTH + j] = a;
-  h1[(size_t)r * WIDTH + j] = silu(a);
+  for (int i = 0; i < D_IN; ++i) a += x[i] * w[i];
+  return a;
 }
 
-__global__ void bias_act_kernel(float* a, const float* b, float* h, size_t total) {
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    const float v = a[e] + b[e % WIDTH];
-    a[e] = v;
-    h[e] = silu(v);
+// h1 = silu(x W1 + b1), thread j = column j, 16 rows per workgroup.
+constexpr int L1R = 16;
+__global__ __launch_bounds__(256) void l1_fwd_kernel(const float* prm, const float* x, const int* idx, int rows,
+                                                     float* h1) {
+  __shared__ float xs[L1R][D_IN];
+  const int j = threadIdx.x, r0 = blockIdx.x * L1R;
+  const int m = rows - r0 < L1R ? rows - r0 : L1R;
+  if (j < m * D_IN) {
+    const int r = r0 + j / D_IN;
+    xs[j / D_IN][j % D_IN] = x[(size_t)(idx ? idx[r] : r) * D_IN + j % D_IN];
   }
+  float wj[D_IN];
+#pragma unroll
+  for (int i = 0; i < D_IN; ++i) wj[i] = prm[OFF_W1 + i * WIDTH + j];
+  const float bj = prm[OFF_B1 + j];
+  __syncthreads();
+  for (int r = 0; r < m; ++r) h1[(size_t)(r0 + r) * WIDTH + j] = silu(layer1(wj, bj, xs[r]));
 }
 
-// out = h2 W3 + b3: one wave per row, lane l holds columns 4l .. 4l+3.
-__global__ __launch_bounds__(256) void l3_fwd_kernel(const float* prm, const float* h2, int rows, float* out) {
+// out = silu(z2 + b2) W3 + b3 (z2 = h1 W2): one wave per row, lane l holds
+// columns 4l .. 4l+3.
+__global__ __launch_bounds__(256) void l3_fwd_kernel(const float* prm, const float* z2, int rows, float* out) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
+  const f4_t z = *(const f4_t*)(z2 + (size_t)r * WIDTH + 4 * lane);
   float s0 = 0.f, s1 = 0.f;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int c = 4 * lane + q;
-    const float h = h2[(size_t)r * WIDTH + c];
+    const float h = silu(z[q] + prm[OFF_B2 + c]);
     s0 += h * prm[OFF_W3 + 2 * c];
     s1 += h * prm[OFF_W3 + 2 * c + 1];
   }
@@ -449,8 +475,11 @@ __global__ __launch_bounds__(256) void loss_partial_kernel(const float* out, con
   }
 }
 
-__global__ __launch_bounds__(256) void loss_final_kernel(const double* part, int nchunk, int rows, double* loss,
-                                                         double* msum_out) {
+// Every workgroup sums the chunks' partial sums (in the same fixed order)
+// and forms the gradients of its rows; the first one also writes the loss.
+__global__ __launch_bounds__(256) void loss_grad_kernel(const float* out, const float* y, const float* ell_t,
+                                                        const float* mask, const int* idx, int rows,
+                                                        const double* part, int nchunk, float* dout, double* loss) {
   __shared__ double sh[256];
   double b = 0.0, m = 0.0, q = 0.0;
   for (int c = threadIdx.x; c < nchunk; c += 256) {
@@ -458,69 +487,124 @@ __global__ __launch_bounds__(256) void loss_final_kernel(const double* part, int
     m += part[3 * (size_t)c + 1];
     q += part[3 * (size_t)c + 2];
   }
-  b = block_sum(b, sh);
   m = block_sum(m, sh);
-  q = block_sum(q, sh);
-  if (threadIdx.x == 0) {
-    const double ms = m > 1.0 ? m : 1.0;
-    *msum_out = ms;
-    if (loss) *loss = b / rows + q / ms;
+  const double ms = m > 1.0 ? m : 1.0;
+  if (blockIdx.x == 0 && loss) {
+    b = block_sum(b, sh);
+    q = block_sum(q, sh);
+    if (threadIdx.x == 0) *loss = b / rows + q / ms;
   }
-}
-
-__global__ void loss_grad_kernel(const float* out, const float* y, const float* ell_t, const float* mask,
-                                 const int* idx, int rows, const double* msum, float* dout) {
   const int r = blockIdx.x * 256 + threadIdx.x;
   if (r >= rows) return;
   const int src = idx ? idx[r] : r;
   const float s = out[2 * (size_t)r], l = out[2 * (size_t)r + 1];
-  const float inv_ms = (float)(1.0 / *msum);
+  const float inv_ms = (float)(1.0 / ms);
   dout[2 * (size_t)r] = (sigm(s) - y[src]) / (float)rows;
   dout[2 * (size_t)r + 1] = 2.f * mask[src] * (l - ell_t[src]) * inv_ms;
 }
 
-// Partial sums over row chunks: part[chunk][t][c] = sum_r L[r][t] D[r][c]
-// for t < T and sum_r D[r][c] for t = T (bias).  L rows may be gathered.
-__global__ __launch_bounds__(256) void rowred_partial_kernel(const float* L, int ldl, const int* lidx, int T,
-                                                             const float* D, int ldd, int C, int rows,
-                                                             float* part) {
-  const int chunk = blockIdx.x;
-  const int r0 = chunk * CHUNK;
-  const int r1 = r0 + CHUNK < rows ? r0 + CHUNK : rows;
-  const int nout = (T + 1) * C;
-  for (int o = threadIdx.x; o < nout; o += 256) {
-    const int t = o / C, c = o % C;
-    float acc = 0.f;
-    for (int r = r0; r < r1; ++r) {
-      const float lv = t < T ? L[(size_t)(lidx ? lidx[r] : r) * ldl + t] : 1.f;
-      acc += lv * D[(size_t)r * ldd + c];
+// Backward of layer 3 and layer 2's activation for CHUNK rows x CG columns:
+// da2 = (dout W3^T) o silu'(a2), and the chunk's sums of dW3 = h2^T dout,
+// db3 and db2.
+__global__ __launch_bounds__(256) void bwd3_kernel(const float* prm, const float* dout, const float* z2, int rows,
+                                                   float* da2, float* part) {
+  __shared__ float hs[CHUNK][CG], ds[CHUNK][CG], go[CHUNK][D_OUT];
+  const int tid = threadIdx.x, c = tid % CG, r0 = blockIdx.x * CHUNK, j = blockIdx.y * CG + c;
+  const int m = rows - r0 < CHUNK ? rows - r0 : CHUNK;
+  for (int e = tid; e < m * D_OUT; e += 256) go[e / D_OUT][e % D_OUT] = dout[(size_t)r0 * D_OUT + e];
+  const float w0 = prm[OFF_W3 + 2 * j], w1 = prm[OFF_W3 + 2 * j + 1], bj = prm[OFF_B2 + j];
+  const float* zc = z2 + (size_t)r0 * WIDTH + j;
+  float z[CHUNK * CG / 256];  // all of the thread's loads in flight at once
+#pragma unroll
+  for (int i = 0; i < CHUNK * CG / 256; ++i) {
+    const int r = tid / CG + i * (256 / CG);
+    z[i] = r < m ? zc[(size_t)r * WIDTH] : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < CHUNK * CG / 256; ++i) {
+    const int r = tid / CG + i * (256 / CG);
+    if (r < m) {
+      const float a = z[i] + bj;
+      const float g = go[r][0] * w0 + go[r][1] * w1;
+      const float d = g * silu_grad(a);
+      da2[(size_t)(r0 + r) * WIDTH + j] = d;
+      ds[r][c] = d;
+      hs[r][c] = silu(a);
     }
-    part[(size_t)chunk * nout + o] = acc;
   }
-}
-__global__ void rowred_final_kernel(const float* part, int nchunk, int T, int C, float* gW, float* gb) {
-  const int nout = (T + 1) * C;
-  const int o = blockIdx.x * 256 + threadIdx.x;
-  if (o >= nout) return;
+  __syncthreads();
+  float* q = part + (size_t)blockIdx.x * PG_LEN;
+  const int k = tid / CG;  // the sum: dW3 of either output, db2, db3
   float acc = 0.f;
-  for (int c = 0; c < nchunk; ++c) acc += part[(size_t)c * nout + o];
-  const int t = o / C;
-  if (t < T) gW[o] = acc;
-  else gb[o - T * C] = acc;
-}
-
-__global__ void da2_kernel(const float* prm, const float* dout, const float* a2, float* da2, size_t total) {
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    const size_t r = e / WIDTH;
-    const int c = (int)(e % WIDTH);
-    const float g = dout[2 * r] * prm[OFF_W3 + 2 * c] + dout[2 * r + 1] * prm[OFF_W3 + 2 * c + 1];
-    da2[e] = g * silu_grad(a2[e]);
+  if (k < D_OUT) {
+#pragma unroll 16
+    for (int r = 0; r < m; ++r) acc += hs[r][c] * go[r][k];
+    q[PG_W3 + D_OUT * j + k] = acc;
+  } else if (k == D_OUT) {
+#pragma unroll 16
+    for (int r = 0; r < m; ++r) acc += ds[r][c];
+    q[PG_B2 + j] = acc;
+  } else if (k == D_OUT + 1 && j < D_OUT) {
+#pragma unroll 16
+    for (int r = 0; r < m; ++r) acc += go[r][j];
+    q[PG_B3 + j] = acc;
   }
 }
 
-__global__ void act_bwd_kernel(float* dh, const float* a, size_t total) {
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256)
-    dh[e] *= silu_grad(a[e]);
+// Backward of layer 1 likewise: da1 = dh1 o silu'(a1), the chunk's sums of
+// dW1 = x^T da1 and db1.
+__global__ __launch_bounds__(256) void bwd1_kernel(const float* prm, const float* dh1, const float* x, const int* idx,
+                                                   int rows, float* part) {
+  __shared__ float xs[CHUNK][D_IN], ds[CHUNK][CG];
+  const int tid = threadIdx.x, c = tid % CG, r0 = blockIdx.x * CHUNK, j = blockIdx.y * CG + c;
+  const int m = rows - r0 < CHUNK ? rows - r0 : CHUNK;
+  for (int e = tid; e < m * D_IN; e += 256) {
+    const int r = r0 + e / D_IN;
+    xs[e / D_IN][e % D_IN] = x[(size_t)(idx ? idx[r] : r) * D_IN + e % D_IN];
+  }
+  float wj[D_IN];
+#pragma unroll
+  for (int i = 0; i < D_IN; ++i) wj[i] = prm[OFF_W1 + i * WIDTH + j];
+  const float bj = prm[OFF_B1 + j];
+  const float* dc = dh1 + (size_t)r0 * WIDTH + j;
+  float d[CHUNK * CG / 256];
+#pragma unroll
+  for (int i = 0; i < CHUNK * CG / 256; ++i) {
+    const int r = tid / CG + i * (256 / CG);
+    d[i] = r < m ? dc[(size_t)r * WIDTH] : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < CHUNK * CG / 256; ++i) {
+    const int r = tid / CG + i * (256 / CG);
+    if (r < m) ds[r][c] = d[i] * silu_grad(layer1(wj, bj, xs[r]));
+  }
+  __syncthreads();
+  float* q = part + (size_t)blockIdx.x * PG_LEN;
+  const int k = tid / CG;  // the sum: dW1 of input k (and db1, by the threads of input 0)
+  static_assert(256 / CG == D_IN, "one thread per input and column");
+  float acc = 0.f;
+#pragma unroll 16
+  for (int r = 0; r < m; ++r) acc += xs[r][k] * ds[r][c];
+  q[PG_W1 + k * WIDTH + j] = acc;
+  if (k == 0) {
+    acc = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < m; ++r) acc += ds[r][c];
+    q[PG_B1 + j] = acc;
+  }
+}
+
+// Sums the partial gradients over the chunks, in their order.
+__global__ __launch_bounds__(64) void grad_sum_kernel(const float* part, int nchunk, float* grads) {
+  const int o = blockIdx.x * 64 + threadIdx.x;
+  if (o >= PG_LEN) return;
+  float acc = 0.f;
+#pragma unroll 16
+  for (int c = 0; c < nchunk; ++c) acc += part[(size_t)c * PG_LEN + o];
+  // (W1, b1) and (b2, W3, b3) lie in the parameters' own order
+  grads[o < PG_B2 ? OFF_W1 + o : OFF_B2 + (o - PG_B2)] = acc;
 }
 
 __global__ void adam_kernel(float* p, const float* g, float* m, float* v, int n, float lr, float b1, float b2,
@@ -683,37 +767,24 @@ int enqueue_select(hipStream_t s, const int32_t n[4], int R, int Rc, const doubl
 
 size_t mlp_ws_bytes(int rows) {
   const size_t act = al(sizeof(float) * (size_t)rows * WIDTH);
-  const int nchunk = (rows + CHUNK - 1) / CHUNK;
-  return 6 * act + al(sizeof(float) * (size_t)nchunk * (D_IN + 1) * WIDTH) + al(sizeof(double) * 3 * (size_t)nchunk) +
-         al(sizeof(double));
+  const size_t nchunk = (rows + CHUNK - 1) / CHUNK;
+  return 4 * act + al(sizeof(float) * nchunk * PG_LEN) + al(sizeof(double) * 3 * nchunk);
 }
 struct MlpWs {
-  float *a1, *h1, *a2, *h2, *d1, *d2, *part;
-  double *lpart, *msum;
+  float *h1, *z2, *d1, *d2, *part;
+  double* lpart;
 };
 MlpWs carve_mlp(void* ws, int rows) {
   Carve c{(char*)ws};
-  const size_t act = (size_t)rows * WIDTH;
-  const int nchunk = (rows + CHUNK - 1) / CHUNK;
+  const size_t act = (size_t)rows * WIDTH, nchunk = (rows + CHUNK - 1) / CHUNK;
   MlpWs w;
-  w.a1 = c.take<float>(act);
   w.h1 = c.take<float>(act);
-  w.a2 = c.take<float>(act);
-  w.h2 = c.take<float>(act);
+  w.z2 = c.take<float>(act);
   w.d1 = c.take<float>(act);
   w.d2 = c.take<float>(act);
-  w.part = c.take<float>((size_t)nchunk * (D_IN + 1) * WIDTH);
-  w.lpart = c.take<double>(3 * (size_t)nchunk);
-  w.msum = c.take<double>(1);
+  w.part = c.take<float>(nchunk * PG_LEN);
+  w.lpart = c.take<double>(3 * nchunk);
   return w;
-}
-
-void rowred(hipStream_t s, const float* L, int ldl, const int* lidx, int T, const float* D, int ldd, int C,
-            int rows, float* part, float* gW, float* gb) {
-  const int nchunk = (rows + CHUNK - 1) / CHUNK;
-  hipLaunchKernelGGL(rowred_partial_kernel, dim3(nchunk), dim3(256), 0, s, L, ldl, lidx, T, D, ldd, C, rows, part);
-  const int nout = (T + 1) * C;
-  hipLaunchKernelGGL(rowred_final_kernel, dim3((nout + 255) / 256), dim3(256), 0, s, part, nchunk, T, C, gW, gb);
 }
 
 // Scratch of the allocation-free feature entry point: S = X0^T X0
@@ -842,13 +913,11 @@ cpd_status cpd_mlp_forward(const float* params, const float* x, const int32_t* i
   if (workspace_bytes < mlp_ws_bytes(rows)) return CPD_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   MlpWs w = carve_mlp(workspace, rows);
-  const size_t act = (size_t)rows * WIDTH;
-  hipLaunchKernelGGL(l1_fwd_kernel, dim3(rows), dim3(256), 0, s, params, x, idx, rows, w.a1, w.h1);
-  GemmF32 g{rows, WIDTH, WIDTH, w.h1, WIDTH, false, params + OFF_W2, nullptr, WIDTH, false, w.a2, WIDTH, nullptr,
+  hipLaunchKernelGGL(l1_fwd_kernel, dim3((rows + L1R - 1) / L1R), dim3(256), 0, s, params, x, idx, rows, w.h1);
+  GemmF32 g{rows, WIDTH, WIDTH, w.h1, WIDTH, false, params + OFF_W2, nullptr, WIDTH, false, w.z2, WIDTH, nullptr,
             1.f, 0.f, nullptr};
   gemm_f32(s, g);
-  hipLaunchKernelGGL(bias_act_kernel, dim3(grid_of(act)), dim3(256), 0, s, w.a2, params + OFF_B2, w.h2, act);
-  hipLaunchKernelGGL(l3_fwd_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, params, w.h2, rows, out);
+  hipLaunchKernelGGL(l3_fwd_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, params, w.z2, rows, out);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }
 
@@ -861,9 +930,8 @@ cpd_status cpd_mlp_loss(const float* out, const float* y, const float* ell_t, co
   MlpWs w = carve_mlp(workspace, rows);
   const int nchunk = (rows + CHUNK - 1) / CHUNK;
   hipLaunchKernelGGL(loss_partial_kernel, dim3(nchunk), dim3(256), 0, s, out, y, ell_t, mask, idx, rows, w.lpart);
-  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, s, w.lpart, nchunk, rows, loss_dev, w.msum);
   hipLaunchKernelGGL(loss_grad_kernel, dim3((rows + 255) / 256), dim3(256), 0, s, out, y, ell_t, mask, idx, rows,
-                     w.msum, dout);
+                     w.lpart, nchunk, dout, loss_dev);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }
 
@@ -873,22 +941,16 @@ cpd_status cpd_mlp_backward(const float* params, const float* x, const int32_t* 
   if (workspace_bytes < mlp_ws_bytes(rows)) return CPD_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   MlpWs w = carve_mlp(workspace, rows);
-  const size_t act = (size_t)rows * WIDTH;
-  // layer 3: dW3 = h2^T dout, db3 = sum dout
-  rowred(s, w.h2, WIDTH, nullptr, WIDTH, dout, D_OUT, D_OUT, rows, w.part, grads + OFF_W3, grads + OFF_B3);
-  // da2 = (dout W3^T) o silu'(a2)
-  hipLaunchKernelGGL(da2_kernel, dim3(grid_of(act)), dim3(256), 0, s, params, dout, w.a2, w.d2, act);
-  // layer 2: dW2 = h1^T da2, db2 = sum da2, dh1 = da2 W2^T
+  const dim3 chunks((rows + CHUNK - 1) / CHUNK, WIDTH / CG);
+  hipLaunchKernelGGL(bwd3_kernel, chunks, dim3(256), 0, s, params, dout, w.z2, rows, w.d2, w.part);
+  // layer 2: dW2 = h1^T da2, dh1 = da2 W2^T
   GemmF32 gw{WIDTH, WIDTH, rows, w.h1, WIDTH, true, w.d2, nullptr, WIDTH, false, grads + OFF_W2, WIDTH, nullptr,
              1.f, 0.f, nullptr};
-  gemm_f32(s, gw);
-  rowred(s, nullptr, 0, nullptr, 0, w.d2, WIDTH, WIDTH, rows, w.part, nullptr, grads + OFF_B2);
   GemmF32 gd{rows, WIDTH, WIDTH, w.d2, WIDTH, false, params + OFF_W2, nullptr, WIDTH, true, w.d1, WIDTH, nullptr,
              1.f, 0.f, nullptr};
-  gemm_f32(s, gd);
-  // layer 1: da1 = dh1 o silu'(a1), dW1 = x^T da1, db1 = sum da1
-  hipLaunchKernelGGL(act_bwd_kernel, dim3(grid_of(act)), dim3(256), 0, s, w.d1, w.a1, act);
-  rowred(s, x, D_IN, idx, D_IN, w.d1, WIDTH, WIDTH, rows, w.part, grads + OFF_W1, grads + OFF_B1);
+  gemm_f32_two(s, gw, gd);
+  hipLaunchKernelGGL(bwd1_kernel, chunks, dim3(256), 0, s, params, w.d1, x, idx, rows, w.part);
+  hipLaunchKernelGGL(grad_sum_kernel, dim3((PG_LEN + 63) / 64), dim3(64), 0, s, w.part, (int)chunks.x, grads);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }
 

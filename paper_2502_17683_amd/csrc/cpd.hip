@@ -1021,8 +1021,7 @@ int setup_norm2(Prob& q, hipStream_t s) {
   double *A = q.setup[0], *B = q.setup[1], *C = q.setup[2];
   const double* const* X = q.d.X;
   auto syrk = [&](const double* x, int n, double* out) {
-    GemmF64 g{Rt, Rt, n, x, Rt, true, x, nullptr, Rt, false, out, Rt, nullptr, 1.0, 0.0, nullptr};
-    gemm_f64(s, g);
+    syrk_f64(s, Rt, n, x, Rt, out, Rt);
   };
   const size_t cnt = (size_t)Rt * Rt;
   syrk(X[0], q.n[0], A);

@@ -500,6 +500,34 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local, 
   const gptr<T> gP1 = as_global(p.P1), gP2 = as_global(p.P2);
   constexpr int FB = FragB::F;
   typedef T vb __attribute__((ext_vector_type(FB)));
+  if (AT && p.mirror && m0 != n0) {
+    // the transposed tile above the diagonal (AT: a lane's tiles of A are
+    // adjacent rows of C)
+    constexpr int FA = FragA::F;
+    typedef T va __attribute__((ext_vector_type(FA)));
+#pragma unroll
+    for (int b = 0; b < TJ; ++b) {
+      const int col = n0 + wn * WTN + FragB::row(b, lane & 15);
+      if (col >= p.N) continue;
+#pragma unroll
+      for (int a = 0; a < TI; a += FA)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + wm * WTM + FragA::row(a, dsub_row<T>(lane, r));
+          const size_t off = (size_t)col * p.ldc + row;
+          va v;
+#pragma unroll
+          for (int i = 0; i < FA; ++i) v[i] = p.alpha * acc[a + i][b][r];
+          if (p.vec && row + FA <= p.M) {
+            *(gptr<va>)(gC + off) = v;
+          } else {
+#pragma unroll
+            for (int i = 0; i < FA; ++i)
+              if (row + i < p.M) gC[off + i] = v[i];
+          }
+        }
+    }
+  }
 #pragma unroll
   for (int a = 0; a < TI; ++a)
 #pragma unroll
@@ -752,6 +780,15 @@ void gemm_f32_two(hipStream_t s, const GemmF32& g, const GemmF32& h) {
   gemm_set_vec(b);
   const int n1 = gemm_units(a, TileLong::BM), n2 = gemm_units(b, TileMid::BM);
   hipLaunchKernelGGL((gemm_tile_two_kernel<float, TileLong, TileMid>), dim3(n1 + n2), dim3(256), 0, s, a, b, n1);
+}
+
+void syrk_f64(hipStream_t s, int n, int K, const double* X, int ld, double* C, int ldc) {
+  GemmArgs<double> a{n, n, K, X, ld, X, nullptr, ld, C, ldc, nullptr, 1.0, 0.0, nullptr};
+  if (gemm_tile_ok(a, true, false)) {
+    a.lower = 1;
+    a.mirror = 1;
+  }
+  gemm_dispatch<double>(s, a, true, false);
 }
 
 void gemm_f32(hipStream_t s, const GemmF32& g) {

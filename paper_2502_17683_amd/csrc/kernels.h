@@ -51,6 +51,7 @@ struct GemmArgs {
   void* part = nullptr;
   int32_t* cnt = nullptr;
   int32_t vec = 0;
+  int32_t mirror = 0;  // with lower and op(A) = A^T: C is symmetric, and its upper tiles are stored as well
 };
 struct GemmF64 {
   int M, N, K;
@@ -70,6 +71,9 @@ struct GemmF32 {
 };
 void gemm_f64(hipStream_t s, const GemmF64& g);
 void gemm_f32(hipStream_t s, const GemmF32& g);
+// C = X^T X (n x n, X stored K x n): the lower tiles are computed and stored
+// on both sides, which gives the bits of the whole product.
+void syrk_f64(hipStream_t s, int n, int K, const double* X, int ld, double* C, int ldc);
 // Two independent products, op(A) = A^T of the first and op(B) = B^T of the
 // second, side by side where their shapes allow it.
 void gemm_f32_two(hipStream_t s, const GemmF32& g, const GemmF32& h);

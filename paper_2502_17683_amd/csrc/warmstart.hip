@@ -116,6 +116,13 @@ __device__ __forceinline__ T block_sum(T v, T* sh) {
   return r;
 }
 
+// Sums over the rows of a matrix, column by column: a workgroup takes CC
+// columns (whole 128-byte lines) and 256 / CC groups of rows, so that the
+// chip is full and a thread has eight loads in flight (one thread per
+// column, one load at a time, took 98-114 us at 400 x 2000).  The groups'
+// sums are added in a fixed order.
+constexpr int CC = 16, CG_ROWS = 256 / CC;
+
 // ------------------------------------------------------------ features
 __global__ __launch_bounds__(256) void feat_rows_kernel(const double* Z, const double* S, int R, double* raw) {
   __shared__ double sh[256];
@@ -143,23 +150,40 @@ __global__ __launch_bounds__(256) void feat_rows_kernel(const double* Z, const d
   }
 }
 
-__global__ void feat_cols_kernel(const double* X0, int n, int R, double* raw) {
-  const int P = blockIdx.x * 256 + threadIdx.x;
-  if (P >= R) return;
+__global__ __launch_bounds__(256) void feat_cols_kernel(const double* X0, int n, int R, double* raw) {
+  __shared__ double sm[CG_ROWS][CC], s2[CG_ROWS][CC], s4[CG_ROWS][CC];
+  const int c = threadIdx.x % CC, g = threadIdx.x / CC, P = blockIdx.x * CC + c;
   double mx = 0.0, x2 = 0.0, x4 = 0.0;
-  for (int p = 0; p < n; ++p) {
-    const double x = X0[(size_t)p * R + P];
-    if (fabs(x) > mx || x != x) mx = fabs(x);  // NaN sticks
-    x2 += x * x;
-    x4 += (x * x) * (x * x);
+  if (P < R) {
+#pragma unroll 8
+    for (int p = g; p < n; p += CG_ROWS) {
+      const double x = X0[(size_t)p * R + P];
+      if (fabs(x) > mx || x != x) mx = fabs(x);  // NaN sticks
+      x2 += x * x;
+      x4 += (x * x) * (x * x);
+    }
+  }
+  sm[g][c] = mx;
+  s2[g][c] = x2;
+  s4[g][c] = x4;
+  __syncthreads();
+  if (g || P >= R) return;
+  mx = x2 = x4 = 0.0;
+  for (int k = 0; k < CG_ROWS; ++k) {
+    if (sm[k][c] > mx || sm[k][c] != sm[k][c]) mx = sm[k][c];
+    x2 += s2[k][c];
+    x4 += s4[k][c];
   }
   raw[(size_t)P * D_IN + 4] = lg(mx);
   raw[(size_t)P * D_IN + 5] = x4 > 0.0 ? x2 * x2 / ((double)n * x4) : 0.0;
 }
 
-__global__ __launch_bounds__(256) void feat_standardise_kernel(const double* raw, int R, float* feat, double* heur) {
+// (bad, if given, is cleared for the checks that follow)
+__global__ __launch_bounds__(256) void feat_standardise_kernel(const double* raw, int R, float* feat, double* heur,
+                                                               int* bad) {
   __shared__ double sh[256];
   const int f = blockIdx.x;
+  if (bad && f == 0 && threadIdx.x < 2) bad[threadIdx.x] = 0;
   double s = 0.0;
   for (int P = threadIdx.x; P < R; P += 256) s += raw[(size_t)P * D_IN + f];
   const double mu = block_sum(s, sh) / R;
@@ -178,17 +202,21 @@ __global__ __launch_bounds__(256) void feat_standardise_kernel(const double* raw
 }
 
 // ------------------------------------------------------------ selection
+// Rank of every grid point, one wave each, four to a workgroup (one thread
+// per point took 134 us at 2000 points, 8 workgroups).
 template <typename S>
-__global__ void rank_kernel(const S* s, int stride, int R, int Rc, int* perm) {
-  const int P = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void rank_kernel(const S* s, int stride, int R, int Rc, int* perm) {
+  const int P = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (P >= R) return;
   const S sp = s[(size_t)P * stride];
   int cnt = 0;
-  for (int Q = 0; Q < R; ++Q) {
+#pragma unroll 8
+  for (int Q = lane; Q < R; Q += 64) {
     const S sq = s[(size_t)Q * stride];
     cnt += (sq > sp) || (sq == sp && Q < P);
   }
-  if (cnt < Rc) perm[cnt] = P;
+  for (int m = 32; m > 0; m >>= 1) cnt += __shfl_xor(cnt, m);
+  if (lane == 0 && cnt < Rc) perm[cnt] = P;
 }
 
 struct ScatterArgs {
@@ -196,39 +224,55 @@ struct ScatterArgs {
   const double* noise[4];  // nullable: no blend
   double* F[4];
   int n[4];
+  int xn[4];               // the first mode with the same X
 };
 // Column norms for the blend: xn[m][P] of X_m (r_thc per mode) and
-// rn[m][k] of noise_m (r_cp per mode), laid out as 4 x (R + Rc).
-__global__ void blend_norms_kernel(ScatterArgs a, int R, int Rc, double* norms) {
+// rn[m][k] of noise_m (r_cp per mode), laid out as 4 x (R + Rc).  A mode
+// that shares its X with an earlier one uses that one's norms.
+__global__ __launch_bounds__(256) void blend_norms_kernel(ScatterArgs a, int R, int Rc, double* norms) {
+  __shared__ double sh[CG_ROWS][CC];
   const int m = blockIdx.y, z = blockIdx.z;
-  const int c = blockIdx.x * 256 + threadIdx.x;
+  const int c = threadIdx.x % CC, g = threadIdx.x / CC, col = blockIdx.x * CC + c;
   const int cols = z ? Rc : R;
-  if (c >= cols) return;
+  if (blockIdx.x * CC >= cols || (!z && a.xn[m] != m)) return;
   const double* A = z ? a.noise[m] : a.X[m];
   double s = 0.0;
-  for (int p = 0; p < a.n[m]; ++p) {
-    const double v = A[(size_t)p * cols + c];
-    s += v * v;
+  if (col < cols) {
+#pragma unroll 8
+    for (int p = g; p < a.n[m]; p += CG_ROWS) {
+      const double v = A[(size_t)p * cols + col];
+      s += v * v;
+    }
   }
-  norms[(size_t)m * (R + Rc) + (z ? R : 0) + c] = sqrt(s);
+  sh[g][c] = s;
+  __syncthreads();
+  if (g || col >= cols) return;
+  s = 0.0;
+  for (int k = 0; k < CG_ROWS; ++k) s += sh[k][c];
+  norms[(size_t)m * (R + Rc) + (z ? R : 0) + col] = sqrt(s);
 }
 // F_m[p, k] = exp(ell_P) (X_m[p, P] + sigma ||X_m[:, P]|| R_m[p, k] / ||R_m[:, k]||),
-// P = perm[k].  Every element is read and written by one thread, so noise
-// may alias F.
-__global__ void scatter_kernel(ScatterArgs a, int R, int Rc, const int* perm, const float* ell, int stride,
-                               double sigma, const double* norms) {
-  const int m = blockIdx.y;
-  const size_t total = (size_t)a.n[m] * Rc;
-  const double* xn = norms + (size_t)m * (R + Rc);
-  const double* rn = xn + R;
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    const int p = (int)(e / Rc), k = (int)(e % Rc);
-    const int P = perm[k];
-    const double sc = ell ? exp((double)ell[(size_t)P * stride]) : 1.0;
+// P = perm[k], unless *bad.  A thread keeps its column and takes SROWS rows.
+// Every element is read and written by one thread, so noise may alias F.
+constexpr int SROWS = 16;
+__global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a, int R, int Rc, const int* perm, const float* ell,
+                                                      int stride, double sigma, const double* norms, const int* bad) {
+  if (bad && *bad) return;
+  const int m = blockIdx.z, k = blockIdx.x * 256 + threadIdx.x;
+  const int p0 = blockIdx.y * SROWS, p1 = p0 + SROWS < a.n[m] ? p0 + SROWS : a.n[m];
+  if (k >= Rc || p0 >= p1) return;
+  const int P = perm[k];
+  const double sc = ell ? exp((double)ell[(size_t)P * stride]) : 1.0;
+  const double* noise = a.noise[m];
+  const double xs = noise ? sigma * norms[(size_t)a.xn[m] * (R + Rc) + P] : 0.0;
+  const double rn = noise ? norms[(size_t)m * (R + Rc) + R + k] : 0.0;
+#pragma unroll 4
+  for (int p = p0; p < p1; ++p) {
+    const size_t e = (size_t)p * Rc + k;
     double v = a.X[m][(size_t)p * R + P];
-    if (a.noise[m]) {
-      const double unit = rn[k] > 0.0 ? a.noise[m][e] / rn[k] : 0.0;
-      v = v + (sigma * xn[P]) * unit;
+    if (noise) {
+      const double unit = rn > 0.0 ? noise[e] / rn : 0.0;
+      v = v + xs * unit;
     }
     a.F[m][e] = v * sc;
   }
@@ -635,9 +679,11 @@ __global__ void pack_kernel(const float* prm, float* pk, __bf16* w2t) {
   if (e < D_OUT) pk[PK_B3 + e] = prm[OFF_B3 + e];
 }
 
-constexpr int IR = 64;         // rows per workgroup
+// IR rows per workgroup: 64, or 16 where that many workgroups would leave
+// compute units idle (2000 rows: 19.5 us with 64, 9.3 us with 16).
 constexpr int HLD = WIDTH + 8;  // LDS row stride (bf16), keeps 16-byte alignment
 
+template <int IR>
 __global__ __launch_bounds__(256) void infer_bf16_kernel(const float* pk, const __bf16* w2t, const float* x,
                                                          int rows, float* out) {
   __shared__ float xs[IR][D_IN];
@@ -664,28 +710,29 @@ __global__ __launch_bounds__(256) void infer_bf16_kernel(const float* pk, const 
     }
   }
   __syncthreads();
-  f4_t acc[4][4];
+  constexpr int TI = IR / 16;
+  f4_t acc[TI][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
   for (int k0 = 0; k0 < WIDTH; k0 += 32) {
     const int koff = k0 + 8 * (lane >> 4);
-    bf16x8_t a[4], b[4];
+    bf16x8_t a[TI], b[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = *(const bf16x8_t*)&hs[(16 * i + (lane & 15)) * HLD + koff];
+    for (int i = 0; i < TI; ++i) a[i] = *(const bf16x8_t*)&hs[(16 * i + (lane & 15)) * HLD + koff];
 #pragma unroll
     for (int j = 0; j < 4; ++j) b[j] = *(const bf16x8_t*)&w2t[(size_t)(64 * w + 16 * j + (lane & 15)) * WIDTH + koff];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   }
   // h2 = silu(acc + b2); partial out over this lane's columns, then over
   // the 16 lanes of a row group, then over the four waves.
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float s0 = 0.f, s1 = 0.f;
@@ -715,6 +762,15 @@ __global__ __launch_bounds__(256) void infer_bf16_kernel(const float* pk, const 
   }
 }
 
+void infer_bf16(hipStream_t s, const void* packed, const float* x, int rows, float* out) {
+  const float* pk = (const float*)packed;
+  const __bf16* w2t = (const __bf16*)((const char*)packed + PK_W2T_BYTES);
+  if (rows < 64 * 256)
+    hipLaunchKernelGGL(infer_bf16_kernel<16>, dim3((rows + 15) / 16), dim3(256), 0, s, pk, w2t, x, rows, out);
+  else
+    hipLaunchKernelGGL(infer_bf16_kernel<64>, dim3((rows + 63) / 64), dim3(256), 0, s, pk, w2t, x, rows, out);
+}
+
 // ------------------------------------------------------------ workspace layouts
 struct FeatWs {
   double* S;
@@ -724,12 +780,11 @@ FeatWs carve_feat(Carve& c, int R) { return {c.take<double>((size_t)R * R), c.ta
 size_t feat_bytes(int R) { return al(sizeof(double) * (size_t)R * R) + al(sizeof(double) * (size_t)R * D_IN); }
 
 int enqueue_features(hipStream_t s, int n0, int R, const double* X0, const double* Z, float* feat, double* heur,
-                     FeatWs w) {
-  GemmF64 g{R, R, n0, X0, R, true, X0, nullptr, R, false, w.S, R, nullptr, 1.0, 0.0, nullptr};
-  gemm_f64(s, g);
+                     FeatWs w, int* bad = nullptr) {
+  syrk_f64(s, R, n0, X0, R, w.S, R);
   hipLaunchKernelGGL(feat_rows_kernel, dim3(R), dim3(256), 0, s, Z, w.S, R, w.raw);
-  hipLaunchKernelGGL(feat_cols_kernel, dim3((R + 255) / 256), dim3(256), 0, s, X0, n0, R, w.raw);
-  hipLaunchKernelGGL(feat_standardise_kernel, dim3(D_IN), dim3(256), 0, s, w.raw, R, feat, heur);
+  hipLaunchKernelGGL(feat_cols_kernel, dim3((R + CC - 1) / CC), dim3(256), 0, s, X0, n0, R, w.raw);
+  hipLaunchKernelGGL(feat_standardise_kernel, dim3(D_IN), dim3(256), 0, s, w.raw, R, feat, heur, bad);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }
 
@@ -744,24 +799,38 @@ size_t select_bytes(int R, int Rc) { return al(sizeof(int) * (size_t)Rc) + al(si
 
 int enqueue_select(hipStream_t s, const int32_t n[4], int R, int Rc, const double* const X[4], double* const F[4],
                    const int* perm, const float* ell, int stride, const double* const noise[4], double sigma,
-                   double* norms) {
+                   double* norms, const int* bad = nullptr) {
   ScatterArgs a;
-  size_t most = 0;
   int nmax = 0;
   for (int m = 0; m < 4; ++m) {
     a.X[m] = X[m];
     a.noise[m] = (noise && sigma != 0.0) ? noise[m] : nullptr;
     a.F[m] = F[m];
     a.n[m] = n[m];
-    most = (size_t)n[m] * Rc > most ? (size_t)n[m] * Rc : most;
+    a.xn[m] = m;
+    for (int k = m - 1; k >= 0; --k)
+      if (X[k] == X[m] && n[k] == n[m]) a.xn[m] = k;
     nmax = n[m] > nmax ? n[m] : nmax;
   }
   if (a.noise[0]) {
     const int cols = R > Rc ? R : Rc;
-    hipLaunchKernelGGL(blend_norms_kernel, dim3((cols + 255) / 256, 4, 2), dim3(256), 0, s, a, R, Rc, norms);
+    hipLaunchKernelGGL(blend_norms_kernel, dim3((cols + CC - 1) / CC, 4, 2), dim3(256), 0, s, a, R, Rc, norms);
   }
-  hipLaunchKernelGGL(scatter_kernel, dim3(grid_of(most), 4), dim3(256), 0, s, a, R, Rc, perm, ell, stride, sigma,
-                     norms);
+  // (the y extent of a grid ends at 65535)
+  for (int p0 = 0; p0 < nmax; p0 += 65535 * SROWS) {
+    ScatterArgs b = a;
+    int rows = 0;
+    for (int m = 0; m < 4; ++m) {
+      const int left = a.n[m] - p0;
+      b.n[m] = left < 0 ? 0 : left < 65535 * SROWS ? left : 65535 * SROWS;
+      b.X[m] = a.X[m] + (size_t)p0 * R;
+      b.F[m] = a.F[m] + (size_t)p0 * Rc;
+      if (a.noise[m]) b.noise[m] = a.noise[m] + (size_t)p0 * Rc;
+      rows = b.n[m] > rows ? b.n[m] : rows;
+    }
+    hipLaunchKernelGGL(scatter_kernel, dim3((Rc + 255) / 256, (rows + SROWS - 1) / SROWS, 4), dim3(256), 0, s, b, R, Rc,
+                       perm, ell, stride, sigma, norms, bad);
+  }
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }
 
@@ -826,7 +895,7 @@ size_t cpd_ws_workspace_size(int32_t n0, int32_t r_thc, int32_t r_cp) {
   if (n0 <= 0 || r_thc <= 0 || r_cp <= 0 || r_cp > r_thc) return 0;
   const size_t R = r_thc, Rc = r_cp;
   return feat_bytes(r_thc) + al(sizeof(float) * R * D_IN) + al(sizeof(double) * R) + al(sizeof(float) * R * D_OUT) +
-         select_bytes(r_thc, r_cp) + al(sizeof(int)) + al(sizeof(double) * Rc * R) + 2 * al(sizeof(double) * (Rc + R)) +
+         select_bytes(r_thc, r_cp) + al(2 * sizeof(int)) + al(sizeof(double) * Rc * R) + 2 * al(sizeof(double) * (Rc + R)) +
          4 * al(sizeof(int) * (Rc + R));
 }
 
@@ -861,7 +930,7 @@ cpd_status cpd_ws_select_init(const int32_t n[4], int32_t r_thc, int32_t r_cp, c
   Carve c{(char*)workspace};
   int* perm = c.take<int>(r_cp);
   double* norms = c.take<double>(4 * ((size_t)r_thc + r_cp));
-  hipLaunchKernelGGL(rank_kernel<float>, dim3((r_thc + 255) / 256), dim3(256), 0, st, s, stride, r_thc, r_cp, perm);
+  hipLaunchKernelGGL(rank_kernel<float>, dim3((r_thc + 3) / 4), dim3(256), 0, st, s, stride, r_thc, r_cp, perm);
   return enqueue_select(st, n, r_thc, r_cp, X, init, perm, ell, stride, noise, sigma, norms);
 }
 
@@ -977,8 +1046,7 @@ cpd_status cpd_mlp_pack(const float* params, void* packed, void* stream) {
 cpd_status cpd_mlp_infer_bf16(const void* packed, const float* x, int32_t rows, float* out, void* stream) {
   if (!packed || !x || !out || rows <= 0) return CPD_ERR_INVALID_ARG;
   if ((uintptr_t)packed % 256) return CPD_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(infer_bf16_kernel, dim3((rows + IR - 1) / IR), dim3(256), 0, (hipStream_t)stream,
-                     (const float*)packed, (const __bf16*)((const char*)packed + PK_W2T_BYTES), x, rows, out);
+  infer_bf16((hipStream_t)stream, packed, x, rows, out);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }
 
@@ -999,38 +1067,34 @@ cpd_status cpd_ws_init(const int32_t n[4], int32_t r_thc, int32_t r_cp, const do
   float* out = c.take<float>((size_t)R * D_OUT);
   int* perm = c.take<int>(Rc);
   double* norms = c.take<double>(4 * ((size_t)R + Rc));
-  int* bad = c.take<int>(1);
-  int rc = enqueue_features(s, n[0], R, X[0], Z, feat, heur, fw);
+  int* bad = c.take<int>(2);  // non-finite scores of the network, of the heuristic
+  int rc = enqueue_features(s, n[0], R, X[0], Z, feat, heur, fw, bad);
   if (rc != CPD_OK) return rc;
+  // The selection follows its check without a word from the host: with a
+  // non-finite score its last kernel writes nothing, so the noise is intact
+  // for the next source.
   int src = 2;
   int hbad = 1;
   if (packed) {
-    hipLaunchKernelGGL(infer_bf16_kernel, dim3((R + IR - 1) / IR), dim3(256), 0, s, (const float*)packed,
-                       (const __bf16*)((const char*)packed + PK_W2T_BYTES), feat, R, out);
-    WSCHK(hipMemsetAsync(bad, 0, sizeof(int), s));
+    infer_bf16(s, packed, feat, R, out);
     hipLaunchKernelGGL(finite_kernel<float>, dim3(grid_of((size_t)R * D_OUT)), dim3(256), 0, s, out,
                        (size_t)R * D_OUT, bad);
+    hipLaunchKernelGGL(rank_kernel<float>, dim3((R + 3) / 4), dim3(256), 0, s, out, D_OUT, R, Rc, perm);
+    rc = enqueue_select(s, n, R, Rc, X, init, perm, out + 1, D_OUT, noise, sigma, norms, bad);
+    if (rc != CPD_OK) return rc;
     WSCHK(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s));
     WSCHK(hipStreamSynchronize(s));
-    if (!hbad) {
-      hipLaunchKernelGGL(rank_kernel<float>, dim3((R + 255) / 256), dim3(256), 0, s, out, D_OUT, R, Rc, perm);
-      rc = enqueue_select(s, n, R, Rc, X, init, perm, out + 1, D_OUT, noise, sigma, norms);
-      src = 0;
-    }
+    if (!hbad) src = 0;
   }
   if (src == 2) {
-    WSCHK(hipMemsetAsync(bad, 0, sizeof(int), s));
-    hipLaunchKernelGGL(finite_kernel<double>, dim3(grid_of(R)), dim3(256), 0, s, heur, (size_t)R, bad);
-    WSCHK(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    hipLaunchKernelGGL(finite_kernel<double>, dim3(grid_of(R)), dim3(256), 0, s, heur, (size_t)R, bad + 1);
+    hipLaunchKernelGGL(rank_kernel<double>, dim3((R + 3) / 4), dim3(256), 0, s, heur, 1, R, Rc, perm);
+    rc = enqueue_select(s, n, R, Rc, X, init, perm, nullptr, 1, noise, sigma, norms, bad + 1);
+    if (rc != CPD_OK) return rc;
+    WSCHK(hipMemcpyAsync(&hbad, bad + 1, sizeof(int), hipMemcpyDeviceToHost, s));
     WSCHK(hipStreamSynchronize(s));
-    if (!hbad) {
-      hipLaunchKernelGGL(rank_kernel<double>, dim3((R + 255) / 256), dim3(256), 0, s, heur, 1, R, Rc, perm);
-      rc = enqueue_select(s, n, R, Rc, X, init, perm, nullptr, 1, noise, sigma, norms);
-      src = 1;
-    }
+    if (!hbad) src = 1;
   }
-  if (rc != CPD_OK) return rc;
-  WSCHK(hipStreamSynchronize(s));
   if (source) *source = src;
   return CPD_OK;
 }

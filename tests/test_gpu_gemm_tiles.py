@@ -58,3 +58,17 @@ def test_split_products_of_a_plan(dims, r_thc, r_cp, precision):
         assert torch.equal(first, second)
         assert np.all(np.abs(first.cpu().numpy() - ref) <= k * A)
     plan.close()
+
+
+@pytest.mark.parametrize("rows", [1, 17, 16383, 16384, 16400])
+def test_inference_row_tiles(rows):
+    """BF16 inference gives a row the same bits whichever row tile it falls
+    into (16 rows a workgroup below 16384 rows, 64 from there on)."""
+    from paper_2502_17683_amd import WarmStartMLP
+    from synth import mlp_init_params
+    rng = np.random.default_rng(rows)
+    net = WarmStartMLP(mlp_init_params(3))
+    x = torch.as_tensor(rng.standard_normal((rows, 8)).astype(np.float32), device="cuda")
+    out = net.infer_bf16(x)
+    part = torch.cat([net.infer_bf16(x[a:a + 5000].contiguous()) for a in range(0, rows, 5000)])
+    assert torch.equal(out, part) and bool(torch.isfinite(out).all())

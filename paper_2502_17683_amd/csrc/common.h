@@ -28,8 +28,10 @@ enum {
   FLAG_SOLVE_STALL = 4,  // a wait of the dataflow solve passed its spin limit
 };
 
-// Per-plan device state (lives in the caller's workspace).
-struct DevState {
+// Per-problem device state (lives in the caller's workspace).  The states of
+// a plan are one array, so that the host reads them in one copy; a problem's
+// own 256 bytes keep its flags apart from the others'.
+struct alignas(256) DevState {
   double norm2;          // ||G||^2
   double fit_prev;       // fit of the previous sweep (-1 before the first)
   double inner;          // <G, G~> of the last sweep

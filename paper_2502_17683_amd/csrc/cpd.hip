@@ -330,7 +330,6 @@ void carve_mixed(Layout& L, Prob& q, SplitShare& sh) {
 
 void carve_prob(Layout& L, Prob& q, int prec, SplitShare& sh) {
   const int Rt = q.Rt, Tp = q.Tp;
-  q.st = (DevState*)L.take(sizeof(DevState));
   q.st_save = (DevState*)L.take(sizeof(DevState));
   q.fit_hist = (double*)L.take(sizeof(double) * HIST_CAP);
   q.inner_part = (double*)L.take(sizeof(double) * Tp);
@@ -948,7 +947,11 @@ size_t layout_plan(cpd_plan_s* p, char* base) {
   Layout L;
   L.base = base;
   SplitShare sh;
-  for (auto& q : p->P) carve_prob(L, q, p->prec, sh);
+  DevState* sts = (DevState*)L.take(sizeof(DevState) * (size_t)p->count);
+  for (int i = 0; i < p->count; ++i) {
+    p->P[i].st = sts + i;
+    carve_prob(L, p->P[i], p->prec, sh);
+  }
   p->tables_off = L.off;
   p->cnt_off = L.off + align_up(build_tables(p, nullptr, nullptr));
   p->part_off = p->cnt_off + align_up(sizeof(int32_t) * (size_t)p->cnt_count);
@@ -1247,18 +1250,27 @@ int capture(cpd_plan_s* p, bool fit_sweep, bool fast, hipGraph_t* g, hipGraphExe
   return CPD_OK;
 }
 
-__global__ void strided_to_dense_f32(const float* src, int rows, int cols, int ld, double* dst) {
-  const size_t total = (size_t)rows * cols;
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    const size_t r = e / cols, c = e % cols;
-    dst[e] = (double)src[r * ld + c];
-  }
-}
-__global__ void dense_to_strided_f32(const double* src, int rows, int cols, int ld, float* dst) {
-  const size_t total = (size_t)rows * cols;
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    const size_t r = e / cols, c = e % cols;
-    dst[r * ld + c] = (float)src[e];
+// The factors and weights of one problem between the plan's padded rows (ld)
+// and the caller's dense double arrays, all five in one launch (five
+// strided copies took five launches of the runtime's copy kernel: 240 of
+// them, 0.7 ms on the GPU alone, to fetch 48 problems).
+template <typename T>
+struct FactorCopy {
+  T* own[5];
+  double* user[5];  // null: skipped
+  int rows[5];
+  int cols, ld;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void factor_copy_kernel(FactorCopy<T> a, int to_user) {
+  const int m = blockIdx.z, c = blockIdx.x * 256 + threadIdx.x;
+  if (!a.user[m] || c >= a.cols) return;
+  const gptr<T> own = as_global(a.own[m]);
+  const gptr<double> user = as_global(a.user[m]);
+  for (int r = blockIdx.y; r < a.rows[m]; r += gridDim.y) {
+    const size_t o = (size_t)r * a.ld + c, u = (size_t)r * a.cols + c;
+    if (to_user) user[u] = (double)own[o];
+    else own[o] = (T)user[u];
   }
 }
 __global__ void state_set_kernel(DevState* st, double prev_fit, int sweeps) {
@@ -1273,41 +1285,44 @@ __global__ void state_set_kernel(DevState* st, double prev_fit, int sweeps) {
   }
 }
 
-int grid_for(size_t n) {
-  size_t g = (n + 255) / 256;
-  if (g > 8192) g = 8192;
-  if (g < 1) g = 1;
-  return (int)g;
-}
-
-int copy_out(cpd_plan_s* p, const Prob& q, const void* src_typed, int rows, int cols, double* dst,
-             hipStream_t s) {
-  if (p->prec == CPD_FP32) {
-    hipLaunchKernelGGL(strided_to_dense_f32, dim3(grid_for((size_t)rows * cols)), dim3(256), 0, s,
-                       (const float*)src_typed, rows, cols, q.Tp, dst);
-    HIPCHK(hipGetLastError());
-  } else {
-    HIPCHK(hipMemcpy2DAsync(dst, sizeof(double) * cols, src_typed, sizeof(double) * q.Tp, sizeof(double) * cols,
-                            rows, hipMemcpyDeviceToDevice, s));
+template <typename T>
+int factor_copy_typed(const Prob& q, const Bufs<T>& b, double* const F[4], double* lam, bool to_user, hipStream_t s) {
+  FactorCopy<T> a;
+  int most = 1;
+  for (int m = 0; m < 4; ++m) {
+    a.own[m] = b.F[m];
+    a.user[m] = F ? F[m] : nullptr;
+    a.rows[m] = q.n[m];
+    most = q.n[m] > most ? q.n[m] : most;
   }
+  a.own[4] = b.lam;
+  a.user[4] = lam;
+  a.rows[4] = 1;
+  a.cols = q.Rc;
+  a.ld = q.Tp;
+  const int gx = (q.Rc + 255) / 256;
+  const int gy = most < 2048 / gx + 1 ? most : 2048 / gx + 1;
+  hipLaunchKernelGGL((factor_copy_kernel<T>), dim3(gx, gy, 5), dim3(256), 0, s, a, (int)to_user);
+  HIPCHK(hipGetLastError());
   return CPD_OK;
 }
-
-int copy_in(cpd_plan_s* p, const Prob& q, const double* src, int rows, int cols, void* dst_typed, hipStream_t s) {
-  if (p->prec == CPD_FP32) {
-    hipLaunchKernelGGL(dense_to_strided_f32, dim3(grid_for((size_t)rows * cols)), dim3(256), 0, s, src, rows,
-                       cols, q.Tp, (float*)dst_typed);
-    HIPCHK(hipGetLastError());
-  } else {
-    HIPCHK(hipMemcpy2DAsync(dst_typed, sizeof(double) * q.Tp, src, sizeof(double) * cols, sizeof(double) * cols,
-                            rows, hipMemcpyDeviceToDevice, s));
-  }
-  return CPD_OK;
+int factor_copy(cpd_plan_s* p, const Prob& q, double* const F[4], double* lam, bool to_user) {
+  return p->prec == CPD_FP32 ? factor_copy_typed<float>(q, q.b32, F, lam, to_user, p->stream)
+                             : factor_copy_typed<double>(q, q.b64, F, lam, to_user, p->stream);
+}
+// The MTTKRP left in Msol, as dense doubles.
+int copy_msol(cpd_plan_s* p, Prob& q, int mode, double* dst) {
+  Prob t = q;
+  t.b32.F[mode] = q.b32.Msol;
+  t.b64.F[mode] = q.b64.Msol;
+  double* F[4] = {nullptr, nullptr, nullptr, nullptr};
+  F[mode] = dst;
+  return factor_copy(p, t, F, nullptr, true);
 }
 
 int read_states(cpd_plan_s* p) {
-  for (int i = 0; i < p->count; ++i)
-    HIPCHK(hipMemcpyAsync(&p->host_states[i], p->P[i].st, sizeof(DevState), hipMemcpyDeviceToHost, p->stream));
+  HIPCHK(hipMemcpyAsync(p->host_states, p->P[0].st, sizeof(DevState) * (size_t)p->count, hipMemcpyDeviceToHost,
+                        p->stream));
   HIPCHK(hipStreamSynchronize(p->stream));
   return CPD_OK;
 }
@@ -1717,20 +1732,7 @@ int stats_of(cpd_plan_s* p, int idx, cpd_stats_t* out) {
 }
 
 int get_factors_of(cpd_plan_s* p, int idx, double* const F_dev[4], double* lambda_dev) {
-  hipStream_t s = p->stream;
-  const Prob& q = p->P[idx];
-  for (int m = 0; m < 4; ++m) {
-    if (!F_dev || !F_dev[m]) continue;
-    const void* src = p->prec == CPD_FP32 ? (const void*)q.b32.F[m] : (const void*)q.b64.F[m];
-    int rc = copy_out(p, q, src, q.n[m], q.Rc, F_dev[m], s);
-    if (rc != CPD_OK) return rc;
-  }
-  if (lambda_dev) {
-    const void* src = p->prec == CPD_FP32 ? (const void*)q.b32.lam : (const void*)q.b64.lam;
-    int rc = copy_out(p, q, src, 1, q.Rc, lambda_dev, s);
-    if (rc != CPD_OK) return rc;
-  }
-  return CPD_OK;
+  return factor_copy(p, p->P[idx], F_dev, lambda_dev, true);
 }
 
 }  // namespace
@@ -1810,19 +1812,13 @@ cpd_status cpd_set_factors(cpd_plan p, const double* const F_dev[4], const doubl
     if (!F_dev[m]) return CPD_ERR_INVALID_ARG;
   hipStream_t s = p->stream;
   Prob& q = p->P[0];
-  for (int m = 0; m < 4; ++m) {
-    void* dst = p->prec == CPD_FP32 ? (void*)q.b32.F[m] : (void*)q.b64.F[m];
-    int rc = copy_in(p, q, F_dev[m], q.n[m], q.Rc, dst, s);
-    if (rc != CPD_OK) return rc;
-  }
-  if (lambda_dev) {
-    void* dst = p->prec == CPD_FP32 ? (void*)q.b32.lam : (void*)q.b64.lam;
-    int rc = copy_in(p, q, lambda_dev, 1, q.Rc, dst, s);
-    if (rc != CPD_OK) return rc;
-  }
+  double* F[4];
+  for (int m = 0; m < 4; ++m) F[m] = const_cast<double*>(F_dev[m]);  // (read only in this direction)
+  int rc = factor_copy(p, q, F, const_cast<double*>(lambda_dev), false);
+  if (rc != CPD_OK) return rc;
   hipLaunchKernelGGL(state_set_kernel, dim3(1), dim3(64), 0, s, q.st, prev_fit, (int)sweeps);
   HIPCHK(hipGetLastError());
-  int rc = refresh_all(p, s);
+  rc = refresh_all(p, s);
   if (rc != CPD_OK) return rc;
   p->launched = sweeps;
   return CPD_OK;
@@ -1845,14 +1841,14 @@ cpd_status cpd_mttkrp(cpd_plan p, int32_t mode, double* M_dev) {
   Prob& q = p->P[0];
   if (p->prec == CPD_FP64) {
     mttkrp_typed<double>(p, s, q.b64, q.Tp, core, mode);
-    return copy_out(p, q, q.b64.Msol, q.n[mode], q.Rc, M_dev, s);
+    return copy_msol(p, q, mode, M_dev);
   } else if (p->prec == CPD_FP32) {
     mttkrp_typed<float>(p, s, q.b32, q.Tp, core, mode);
-    return copy_out(p, q, q.b32.Msol, q.n[mode], q.Rc, M_dev, s);
+    return copy_msol(p, q, mode, M_dev);
   }
   run_split(p, s, p->score[core]);
   run_split(p, s, p->sback[mode]);
-  return copy_out(p, q, q.b64.Msol, q.n[mode], q.Rc, M_dev, s);
+  return copy_msol(p, q, mode, M_dev);
 }
 
 cpd_status cpd_kernel_times(cpd_plan p, int32_t reps, double* ms_out) {

@@ -956,6 +956,7 @@ __device__ __forceinline__ bool poll_flags(const int32_t* a, const int32_t* b, i
   }
 }
 static int g_bwd_form = 0;  // host side: 0 block pairs, 1 one block column per hop
+int get_bwd_form() { return g_bwd_form; }
 int set_bwd_form(int form) {
   const int prev = g_bwd_form;
   g_bwd_form = form == 1 ? 1 : 0;
@@ -1074,7 +1075,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void flow_reset_kernel(const StepProb<T>* probs) {
   const StepProb<T>& q = probs[blockIdx.x];
   const int cnt = ((q.n + TB - 1) / TB) * q.nblk;
-  const gptr<int32_t> f = as_global(q.flow);
+  const gptr<int32_t> f = as_global(q.bflow);
   for (int e = threadIdx.x; e < cnt; e += 256) f[e] = 0;
 }
 
@@ -1092,9 +1093,16 @@ __device__ __forceinline__ void flow_segment(const int* seg, int nseg, int bx, i
   bid = bx - seg[3 * lo];
 }
 
+// A problem in the inverse form takes the backward solve only in the
+// damped-retry pass, whose forward solve forms no inverse.
+template <typename T>
+__device__ __forceinline__ bool skip_bwd(const StepProb<T>& q, int slow) {
+  return q.E && !(slow && q.st->retry_active);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256, 2) void bwd_flow_kernel(const StepProb<T>* probs, const int* seg, int nseg,
-                                                       int spin_limit) {
+                                                       int spin_limit, int slow) {
   typedef typename Acc4<T>::type acc_t;
   __shared__ T S0[TB * LDT];
   __shared__ T S1[TB * LDT];
@@ -1105,11 +1113,11 @@ __global__ __launch_bounds__(256, 2) void bwd_flow_kernel(const StepProb<T>* pro
   DevState* const st = q.st;
   // uniform per problem and unchanged during the launch: all or none of a
   // problem's workgroups take part
-  if (st->done) return;
+  if (st->done || skip_bwd(q, slow)) return;
   const int nblk = q.nblk, Tp = nblk * TB;
   const int r0 = rt * TB, nrows = min(TB, q.n - r0);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int32_t* const flag = q.flow + (size_t)rt * nblk;
+  int32_t* const flag = q.bflow + (size_t)rt * nblk;
   T* const tile = q.M + (size_t)r0 * Tp + (size_t)k * TB;
   acc_t acc[4];
   T rf[16], rl[16], rx[16];
@@ -1248,14 +1256,15 @@ __device__ __forceinline__ void tile_mma64_ra2(typename Acc4<T>::type acc[4], co
 // One product of the pair set-up per workgroup (output o of pair j): the
 // result goes to an upper block of V.
 template <typename T>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(const StepProb<T>* probs, const int* offs, int nprob) {
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const StepProb<T>* probs, const int* offs, int nprob,
+                                                          int slow) {
   typedef typename Acc4<T>::type acc_t;
   __shared__ T S0[TB * LDT];
   __shared__ T S1[TB * LDT];
   int pid = 0;
   while (pid + 1 < nprob && (int)blockIdx.x >= offs[pid + 1]) ++pid;
   const StepProb<T> q = probs[pid];
-  if (q.st->done) return;  // as the backward launch that reads the results
+  if (q.st->done || skip_bwd(q, slow)) return;  // as the backward launch that reads the results
   const int local = blockIdx.x - offs[pid], j = local / 5, o = local % 5;
   const int nblk = q.nblk, Tp = nblk * TB;
   const int b = nblk - 1 - 2 * j, a = b - 1, c = b + 1, d = b + 2;
@@ -1321,7 +1330,7 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const StepProb<T>* probs,
 
 template <typename T>
 __global__ __launch_bounds__(256, 2) void bwd_pair_kernel(const StepProb<T>* probs, const int* seg, int nseg,
-                                                       int spin_limit) {
+                                                       int spin_limit, int slow) {
   typedef typename Acc4<T>::type acc_t;
   __shared__ T S0[TB * LDT];
   __shared__ T S1[TB * LDT];
@@ -1332,7 +1341,7 @@ __global__ __launch_bounds__(256, 2) void bwd_pair_kernel(const StepProb<T>* pro
   DevState* const st = q.st;
   // uniform per problem and unchanged during the launch: all or none of a
   // problem's workgroups take part
-  if (st->done) return;
+  if (st->done || skip_bwd(q, slow)) return;
   const int nblk = q.nblk, Tp = nblk * TB;
   const int hb = nblk - 1 - 2 * j, ha = hb - 1, c = hb + 1, d = hb + 2;
   const bool has_a = ha >= 0, has_q = j >= 1;
@@ -1341,7 +1350,7 @@ __global__ __launch_bounds__(256, 2) void bwd_pair_kernel(const StepProb<T>* pro
   const int k = role_a ? ha : hb;
   const int r0 = rt * TB, nrows = min(TB, q.n - r0);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int32_t* const flag = q.flow + (size_t)rt * nblk;
+  int32_t* const flag = q.bflow + (size_t)rt * nblk;
   T* const rowp = q.M + (size_t)r0 * Tp;
   auto tile = [&](int x) { return rowp + (size_t)x * TB; };
   auto vblk = [&](int x, int y) { return q.V + (size_t)x * TB * Tp + (size_t)y * TB; };
@@ -1474,6 +1483,13 @@ __global__ __launch_bounds__(256, 2) void bwd_pair_kernel(const StepProb<T>* pro
 // id (columns in order; in a column the diagonal tile first, the forward
 // tiles last), so the launch cannot deadlock; waits are bounded as in the
 // backward solve.
+//
+// Inverse form (StepProb::E): the rows of the identity ride through the
+// forward solve as further row tiles, tile (t, k) for t < k.  They end with
+// the last column, as the other row tiles do, and run on units that a small
+// problem leaves idle; the backward solve, a chain of block columns of its
+// own (set-up 17 us and 36 us at n = 100, R_cp = 400), is then one product
+// with E (8 us).
 template <typename T>
 __device__ __forceinline__ void load_acc_coherent(typename Acc4<T>::type acc[4], const T* g, size_t ld, int lane,
                                                   int w) {
@@ -1495,8 +1511,8 @@ template <typename T>
 __global__ __launch_bounds__(256) void cflow_reset_kernel(const StepProb<T>* probs) {
   const StepProb<T>& q = probs[blockIdx.x];
   const int nf = ((q.n + TB - 1) / TB) * q.nblk, nc = (q.nblk + 2) * q.nblk + CU_SLOTS;
-  const gptr<int32_t> f = as_global(q.flow), c = as_global(q.cflow);
-  for (int e = threadIdx.x; e < nf; e += 256) f[e] = 0;
+  const gptr<int32_t> f = as_global(q.flow), c = as_global(q.cflow), b = as_global(q.bflow);
+  for (int e = threadIdx.x; e < nf; e += 256) f[e] = b[e] = 0;
   for (int e = threadIdx.x; e < nc; e += 256) c[e] = 0;
 }
 
@@ -1538,7 +1554,7 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
   // this launch sets it, and a workgroup that left on it would never
   // publish its flags.  A failed problem's tiles are discarded later.)
   if (st->done) return;
-  const int nblk = q.nblk, Tp = nblk * TB, nrt = (q.n + TB - 1) / TB;
+  const int nblk = q.nblk, Tp = nblk * TB;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wu = __builtin_amdgcn_readfirstlane(w);  // wave-uniform
   const int sr = tid >> 2, q0 = tid & 3;   // strip layout (diagonal factorisation)
@@ -1713,21 +1729,32 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
       for (int v = 0; v < 4; ++v) s[4 * ii + v] = (4 * bg + ii == bj + 16 * v) ? T(1) : T(0);
     b4_fwd<T>(s, S1, invd, bj);  // X_k
     store_b4_coherent<T>(s, q.ldiag + (size_t)k * TB * TB, TB, bg, bj);
+    if (q.E) store_b4_coherent<T>(s, q.E + (size_t)k * TB * Tp + (size_t)k * TB, Tp, bg, bj);
     publish(xfl + k);
     return;
   }
 
-  // ---- forward-solve tile (rt, k)
-  const int rt = bid - (nblk - k);
-  const int r0 = rt * TB, nrows = min(TB, q.n - r0);
-  int32_t* const gfl = q.flow + (size_t)rt * nblk;
-  T* const tile = q.M + (size_t)r0 * Tp + (size_t)k * TB;
-  load_acc<T>(acc, tile, Tp, nrows, lane, w);  // M_k, written before the launch
+  // ---- forward-solve tile (rt, k); past the row tiles, the tile (t, k),
+  // t < k, of the solution E = L^{-T} of the identity's rows (E_tt = X_t)
+  const int rt = bid - (nblk - k), nrt = (q.n + TB - 1) / TB;
+  const bool inv = rt >= nrt;
+  const int r0 = inv ? (rt - nrt) * TB : rt * TB, nrows = inv ? TB : min(TB, q.n - r0);
+  const int j0 = inv ? rt - nrt : 0;
+  // (E's flags are the factorisation's unused upper ones)
+  int32_t* const gfl = inv ? lfl + j0 * nblk : q.flow + (size_t)rt * nblk;
+  T* const row = (inv ? q.E : q.M) + (size_t)r0 * Tp;
+  T* const tile = row + (size_t)k * TB;
+  if (inv) {
+#pragma unroll
+    for (int tj = 0; tj < 4; ++tj) acc[tj] = acc_t{0, 0, 0, 0};
+  } else {
+    load_acc<T>(acc, tile, Tp, nrows, lane, w);  // M_k, written before the launch
+  }
 #pragma unroll
   for (int tj = 0; tj < 4; ++tj) p[tj] = acc_t{0, 0, 0, 0};
-  for (int j = 0; j < k; ++j) {
-    if (!wait_acc(gfl + j, lfl + k * nblk + j)) return;
-    fetch_block2_coherent<T>(ra, q.M + (size_t)r0 * Tp + (size_t)j * TB, Tp, nrows, tid);  // G_j
+  for (int j = j0; j < k; ++j) {
+    if (!wait_acc(inv && j == j0 ? xfl + j : gfl + j, lfl + k * nblk + j)) return;
+    fetch_block2_coherent<T>(ra, row + (size_t)j * TB, Tp, nrows, tid);  // G_j
     fetch_block2_coherent<T>(rb, blk(k, j), Tp, TB, tid);                                 // L_kj
     put_block2<T, true>(S0, ra, tid);
     put_block2<T, true>(S1, rb, tid);
@@ -1756,7 +1783,8 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
   publish(gfl + k);
 }
 
-std::vector<int> flow_segments(int mode, const std::vector<int>& nblk, const std::vector<int>& n) {
+std::vector<int> flow_segments(int mode, const std::vector<int>& nblk, const std::vector<int>& n,
+                               const std::vector<char>& inv) {
   std::vector<int> seg;
   int start = 0, cmax = 0;
   for (int b : nblk) cmax = b > cmax ? b : cmax;
@@ -1778,7 +1806,7 @@ std::vector<int> flow_segments(int mode, const std::vector<int>& nblk, const std
       seg.push_back(start);
       seg.push_back((int)p);
       seg.push_back(k);
-      start += mode == STEP_BWD_FLOW ? nrt : nblk[p] - k + nrt;
+      start += mode == STEP_BWD_FLOW ? nrt : nblk[p] - k + nrt + (inv[p] ? k : 0);
     }
   seg.push_back(start);
   seg.push_back(-1);
@@ -1821,7 +1849,7 @@ void step_group(hipStream_t s, int mode, const StepProb<T>* probs, const int* of
       hipLaunchKernelGGL((flow_reset_kernel<T>), dim3(nprob), block, 0, s, probs);
       break;
     case STEP_BWD_FLOW:  // offs: segment table, nprob: its segment count
-      hipLaunchKernelGGL((bwd_flow_kernel<T>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit);
+      hipLaunchKernelGGL((bwd_flow_kernel<T>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit, retry_pass);
       break;
     case STEP_CFLOW_RESET:  // one workgroup per problem
       hipLaunchKernelGGL((cflow_reset_kernel<T>), dim3(nprob), block, 0, s, probs);
@@ -1830,10 +1858,10 @@ void step_group(hipStream_t s, int mode, const StepProb<T>* probs, const int* of
       hipLaunchKernelGGL((chol_fwd_flow_kernel<T>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit);
       break;
     case STEP_BWD_PREP:
-      hipLaunchKernelGGL((bwd_prep_kernel<T>), grid, block, 0, s, probs, offs, nprob);
+      hipLaunchKernelGGL((bwd_prep_kernel<T>), grid, block, 0, s, probs, offs, nprob, retry_pass);
       break;
     case STEP_BWD_PAIR:  // offs: segment table, nprob: its segment count
-      hipLaunchKernelGGL((bwd_pair_kernel<T>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit);
+      hipLaunchKernelGGL((bwd_pair_kernel<T>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit, retry_pass);
       break;
     default:
       hipLaunchKernelGGL((step_kernel<T, STEP_CHOL_FWD>), grid, block, 0, s, probs, offs, nprob, cfg,

@@ -61,11 +61,14 @@ struct Bufs {
   int32_t* flow;   // ready flags of the dataflow solves
   int32_t* cflow;  // ready flags of the dataflow factorisation
   T* dpart;        // partly updated diagonal blocks of the dataflow factorisation
+  int32_t* bflow;  // ready flags of the dataflow backward solve
+  T* E;            // L^{-T} (inverse form of the backward solve) or null
 };
 
 struct Prob {
   cpd_desc d;
   int n[4], Rt, Rc, Tp, nblk, nmax;
+  bool inv;  // backward solve in the inverse form
   Bufs<double> b64;
   Bufs<float> b32;
   MixedBufs mx;
@@ -116,6 +119,7 @@ struct StepOps {
   void* probs = nullptr;                // StepProb<T>[nprob]
   std::vector<SolveLaunch> cholfwd;     // factorisation fused with the forward solve
   std::vector<SolveLaunch> bwd;         // backward solve
+  GroupOp binv, binv_slow;              // ... of the problems in the inverse form: F = G E^T
   std::vector<SolveLaunch> chol_retry;  // damped-retry factorisation (retried problems only)
   std::vector<SolveLaunch> fwd_retry;   // forward solve of the retried problems only
   void* mkeep = nullptr;                // CkptArgs: Msol -> Mbak
@@ -264,6 +268,8 @@ void carve_typed(Layout& L, Prob& q, Bufs<T>& b) {
   b.flow = (int32_t*)L.take(sizeof(int32_t) * (size_t)((q.nmax + 63) / 64) * q.nblk);
   b.cflow = (int32_t*)L.take(sizeof(int32_t) * ((size_t)(q.nblk + 2) * q.nblk + CU_SLOTS));
   b.dpart = (T*)L.take(sizeof(T) * (size_t)q.nblk * 64 * 64);
+  b.bflow = (int32_t*)L.take(sizeof(int32_t) * (size_t)((q.nmax + 63) / 64) * q.nblk);
+  b.E = q.inv ? (T*)L.take(sizeof(T) * (size_t)Tp * Tp) : nullptr;
 }
 
 // Split-BF16 buffers; X and Z splits are shared between problems (and
@@ -412,7 +418,8 @@ std::vector<int> gemm_entries(TableBuilder& tb, std::vector<GemmArgs<T>>& v, int
 }
 
 template <typename T>
-GroupOp gemm_op(TableBuilder& tb, std::vector<GemmArgs<T>> v, bool at, bool bt, const std::string& kind) {
+GroupOp gemm_op(TableBuilder& tb, std::vector<GemmArgs<T>> v, bool at, bool bt, const std::string& kind,
+                bool split = true) {
   GroupOp op;
   op.a_t = at;
   op.b_t = bt;
@@ -421,7 +428,7 @@ GroupOp gemm_op(TableBuilder& tb, std::vector<GemmArgs<T>> v, bool at, bool bt, 
   std::stable_sort(v.begin(), v.end(), [](const GemmArgs<T>& x, const GemmArgs<T>& y) { return x.K > y.K; });
   std::vector<int> dims;
   for (auto& g : v) {
-    gemm_plan_slices(g);
+    if (split) gemm_plan_slices(g);
     gemm_set_vec(g);
     dims.push_back(g.M);
     dims.push_back(g.N);
@@ -615,7 +622,9 @@ std::vector<SolveLaunch> build_sched(TableBuilder& tb, int sched, int max_nblk, 
         nb.push_back(q.nblk);
         nr.push_back(q.n);
       }
-      const std::vector<int> seg = flow_segments(it.mode, nb, nr);
+      std::vector<char> inv;
+      for (auto& q : sp) inv.push_back(q.E != nullptr);
+      const std::vector<int> seg = flow_segments(it.mode, nb, nr, inv);
       L.nseg = (int)seg.size() / 3 - 1;
       L.total = seg[3 * L.nseg];
       L.offs = (int*)tb.put(seg);
@@ -655,7 +664,7 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
   const int np = p->count;
   const std::string kind = sizeof(T) == 8 ? "f64" : "f32";
   for (int n = 0; n < 4; ++n) {
-    std::vector<GemmArgs<T>> core, back, gram, proj;
+    std::vector<GemmArgs<T>> core, back, gram, proj, binv, binv_slow;
     std::vector<StepProb<T>> sp;
     std::vector<FormVArgs<T>> fv;
     std::vector<NormArgs<T>> nm;
@@ -708,13 +717,21 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
             v->back().want = 1;
           }
       }
-      sp.push_back({b.V, b.ldiag, b.diagL, b.Msol, q.st, q.nblk, q.n[n], b.flow, b.cflow, b.dpart});
+      sp.push_back({b.V, b.ldiag, b.diagL, b.Msol, q.st, q.nblk, q.n[n], b.flow, b.cflow, b.dpart, b.bflow, b.E});
+      if (q.inv) {
+        GemmArgs<T> g{q.n[n], Rc, Tp, b.Msol, Tp, b.E, nullptr, Tp, b.F[n], Tp, nullptr, T(1), T(0), done};
+        g.kdiag = 1;
+        binv.push_back(g);
+        g.gate = &q.st->retry_active;
+        binv_slow.push_back(g);
+      }
       const T* g[3];
       int c = 0;
       for (int m = 0; m < 4; ++m)
         if (m != n) g[c++] = b.G[m];
-      fv.push_back({b.V, g[0], g[1], g[2], q.st, Tp, Rc});
-      nm.push_back({b.Msol, b.F[n], b.lam, nullptr, nullptr, q.st, q.n[n], Rc, Tp});
+      fv.push_back({b.V, g[0], g[1], g[2], q.st, Tp, Rc, b.flow, b.cflow, b.bflow, (q.n[n] + 63) / 64 * q.nblk,
+                    (q.nblk + 2) * q.nblk + CU_SLOTS});
+      nm.push_back({b.Msol, b.F[n], b.lam, nullptr, nullptr, q.st, q.n[n], Rc, Tp, q.inv});
     }
     if (n == 0 || n == 2) p->core[n] = gemm_op<T>(tb, core, n == 2, false, kind + "core");
     p->back[n] = gemm_op<T>(tb, back, false, false, kind + "back");
@@ -729,6 +746,8 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
     so.chol_retry = build_sched<T>(tb, SCHED_CHOL, p->maxNblk, pw, sp, 2, kind);
     so.cholfwd = build_sched<T>(tb, SCHED_CHOL_FWD, p->maxNblk, pw, sp, 1, kind);
     so.bwd = build_sched<T>(tb, SCHED_BWD, p->maxNblk, pw, sp, 0, kind);
+    so.binv = gemm_op<T>(tb, binv, false, true, kind + "binv", false);
+    so.binv_slow = gemm_op<T>(tb, binv_slow, false, true, kind + "binv", false);
     so.fwd_retry = build_sched<T>(tb, SCHED_FWD, p->maxNblk, pw, sp, 2, kind);
     {
       std::vector<CkptArgs> keep, restore;
@@ -958,6 +977,26 @@ size_t layout_plan(cpd_plan_s* p, char* base) {
   return p->part_off + p->part_bytes;
 }
 
+// Backward solve of a problem by the inverse form (StepProb::E), from its
+// own shape and precision:
+//   - up to INV_BLOCKS block columns.  The identity's rows are nblk^2 / 2
+//     more tiles of the forward solve, free while they find idle units.  A
+//     sweep of one problem alone, inverse form against block pairs: R_cp =
+//     256 517 : 615 us, 400 772 : 937, 640 1068 : 1258, 1000 1705 : 1966; a
+//     batch that fills the chip: 32 x R_cp 400 2063 : 2114, 16 x 640 2427 :
+//     2423, 16 x 768 3209 : 3125, 16 x 960 4786 : 4449.  (The choice may not
+//     look at the batch: a problem gives the same bits alone and in any.)
+//   - FP64 plans only.  FP32 and split-BF16 plans keep the rounding of the
+//     substitution: their low-precision products carry a last bit on (a
+//     sweep of the Laplace batch moved by 9e-5).
+// The solution's error is that of the substitution (collinear factors, R_cp
+// 100 .. 500, cond(V) 3e4 .. 6e6: 1.7e-12 .. 2.5e-10 either way); the
+// residual is not as small (4e-16 against 6e-16 .. 2e-13).
+constexpr int INV_BLOCKS = 10;
+bool inverse_form(const Prob& q, int prec, int panel) {
+  return prec == CPD_FP64 && panel <= 0 && get_bwd_form() == 0 && q.nblk <= INV_BLOCKS;
+}
+
 int init_shape(cpd_plan_s* p, const cpd_desc* descs, int count) {
   if (count <= 0 || count > 4096 || !descs) return CPD_ERR_INVALID_ARG;
   p->count = count;
@@ -979,6 +1018,7 @@ int init_shape(cpd_plan_s* p, const cpd_desc* descs, int count) {
     }
   }
   if (p->tied && p->prec == CPD_MIXED_BF16) return CPD_ERR_UNSUPPORTED;
+  for (auto& q : p->P) q.inv = inverse_form(q, p->prec, descs[0].solve_panel);
   p->fit_every = descs[0].fit_every > 0 ? descs[0].fit_every : 1;
   p->allow_fallback = descs[0].chol_fallback;
   p->use_graph = descs[0].use_graph;
@@ -1097,12 +1137,23 @@ void run_split(cpd_plan_s* p, hipStream_t s, const GroupOp& op) {
   if (op.kparts > 1) gemm_split_reduce_group(s, tab, op.count, op.kparts, op.maxm, op.maxn);
 }
 template <typename T>
-void run_sched(cpd_plan_s* p, hipStream_t s, int n, const std::vector<SolveLaunch>& sched, int retry_pass) {
+void run_sched(cpd_plan_s* p, hipStream_t s, int n, const std::vector<SolveLaunch>& sched, int retry_pass,
+               bool resets = false) {
   const StepProb<T>* probs = (const StepProb<T>*)p->steps[n].probs;
   for (const SolveLaunch& L : sched) {
+    // (the launch that forms V has cleared the ready flags)
+    if (!resets && (L.mode == STEP_CFLOW_RESET || L.mode == STEP_FLOW_RESET)) continue;
     if (L.mode < 0) run_gemm<T>(p, s, L.gemm);
     else step_group<T>(s, L.mode, probs, L.offs, L.nseg > 0 ? L.nseg : p->count, L.total, L.cfg, retry_pass);
   }
+}
+
+// Backward solve; slow: after the damped-retry pass.
+template <typename T>
+void run_bwd(cpd_plan_s* p, int n, hipStream_t s, bool slow, bool resets = false) {
+  StepOps& so = p->steps[n];
+  if (slow || so.binv.count < p->count) run_sched<T>(p, s, n, so.bwd, slow, resets);
+  if (so.binv.count) run_gemm<T>(p, s, slow ? so.binv_slow : so.binv);
 }
 
 template <typename T>
@@ -1112,7 +1163,7 @@ void solve_mode(cpd_plan_s* p, int n, hipStream_t s, bool with_inner, bool fast)
   form_v_group<T>(s, fv, p->count, p->maxTp, 0);
   if (fast) {
     run_sched<T>(p, s, n, so.cholfwd, 0);
-    run_sched<T>(p, s, n, so.bwd, 0);
+    run_bwd<T>(p, n, s, false);
   } else {
     // Asynchronous sweeps cannot be replayed from the host, so the damped
     // retry stays in the graph: the fused factorisation and forward solve
@@ -1126,9 +1177,9 @@ void solve_mode(cpd_plan_s* p, int n, hipStream_t s, bool with_inner, bool fast)
     run_sched<T>(p, s, n, so.chol_retry, 1);
     checkpoint_group(s, (const CkptArgs*)so.mrestore, p->count, 1);
     run_sched<T>(p, s, n, so.fwd_retry, 1);
-    run_sched<T>(p, s, n, so.bwd, 0);
+    run_bwd<T>(p, n, s, true);
   }
-  normalise_group<T>(s, (const NormArgs<T>*)(with_inner ? p->norm_inner : p->norm[n]), p->count, p->maxR);
+  normalise_group<T>(s, (const NormArgs<T>*)(with_inner ? p->norm_inner : p->norm[n]), p->count, p->maxR, !fast);
 }
 
 // Particle-tied sweep (symmetric ALS): modes 0 and 2 are updated, each
@@ -1873,13 +1924,13 @@ cpd_status cpd_kernel_times(cpd_plan p, int32_t reps, double* ms_out) {
         if (f32) {
           if (which != 6) form_v_group<float>(s, (const FormVArgs<float>*)p->formv[0], p->count, p->maxTp, 0);
           if (which != 6) run_sched<float>(p, s, 0, p->steps[0].cholfwd, 0);
-          if (which != 5) run_sched<float>(p, s, 0, p->steps[0].bwd, 0);
-          if (which == 4) normalise_group<float>(s, (const NormArgs<float>*)p->norm[0], p->count, p->maxR);
+          if (which != 5) run_bwd<float>(p, 0, s, false, which == 6);
+          if (which == 4) normalise_group<float>(s, (const NormArgs<float>*)p->norm[0], p->count, p->maxR, 0);
         } else {
           if (which != 6) form_v_group<double>(s, (const FormVArgs<double>*)p->formv[0], p->count, p->maxTp, 0);
           if (which != 6) run_sched<double>(p, s, 0, p->steps[0].cholfwd, 0);
-          if (which != 5) run_sched<double>(p, s, 0, p->steps[0].bwd, 0);
-          if (which == 4) normalise_group<double>(s, (const NormArgs<double>*)p->norm[0], p->count, p->maxR);
+          if (which != 5) run_bwd<double>(p, 0, s, false, which == 6);
+          if (which == 4) normalise_group<double>(s, (const NormArgs<double>*)p->norm[0], p->count, p->maxR, 0);
         }
         return;
       }

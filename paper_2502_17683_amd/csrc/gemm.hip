@@ -359,7 +359,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local, 
   // unsplit tiles first, then the slices of the others
   int tile, slice = 0, kbeg = 0, kend = p.K;
   if (local < nfull) {
-    tile = xcd_remap(local, nfull);
+    tile = p.kdiag ? local : xcd_remap(local, nfull);
   } else {
     tile = nfull + (local - nfull) / p.slices;
     slice = (local - nfull) % p.slices;
@@ -374,12 +374,17 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs<T>& p, int local, 
     while (r * (r + 1) / 2 > tile) --r;
     m0 = r * BM;
     n0 = (tile - r * (r + 1) / 2) * BN;
+  } else if (p.kdiag) {
+    // the columns with the longest sums first
+    m0 = tile % tiles_m * BM;
+    n0 = tile / tiles_m * BN;
   } else {
     int tm, tn;
     grouped_tile(tile, tiles_m, tiles_n, 8, tm, tn);
     m0 = tm * BM;
     n0 = tn * BN;
   }
+  if (p.kdiag) kbeg = n0 & ~63;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int wm = w / C::WN, wn = w % C::WN;

@@ -56,7 +56,7 @@ size_t solve_ws(int R, int n) {
   const int nblk = (R + 63) / 64, Tp = nblk * 64;
   return al(sizeof(DevState)) + al(sizeof(T) * (size_t)Tp * Tp) + al(sizeof(T) * (size_t)nblk * 4096) +
          al(sizeof(T) * Tp) + al(sizeof(T) * (size_t)n * Tp) + al(sizeof(StepProb<T>)) + al(sizeof(int) * 3 * (nblk + 1)) +
-         al(sizeof(GemmArgs<T>)) + al(sizeof(int32_t) * (size_t)((n + 63) / 64) * nblk) +
+         al(sizeof(GemmArgs<T>)) + 2 * al(sizeof(int32_t) * (size_t)((n + 63) / 64) * nblk) +
          al(sizeof(int32_t) * ((size_t)(nblk + 2) * nblk + CU_SLOTS)) + al(sizeof(T) * (size_t)nblk * 4096);
 }
 
@@ -76,12 +76,13 @@ cpd_status solve_impl(int R, int n, const T* V, const T* M, T* F, void* ws, hipS
   int* offs = (int*)b; b += al(sizeof(int) * 3 * (nblk + 1));
   GemmArgs<T>* gtab = (GemmArgs<T>*)b; b += al(sizeof(GemmArgs<T>));
   int32_t* flow = (int32_t*)b; b += al(sizeof(int32_t) * (size_t)((n + 63) / 64) * nblk);
+  int32_t* bflow = (int32_t*)b; b += al(sizeof(int32_t) * (size_t)((n + 63) / 64) * nblk);
   int32_t* cflow = (int32_t*)b; b += al(sizeof(int32_t) * ((size_t)(nblk + 2) * nblk + CU_SLOTS));
   T* dpart = (T*)b;
   hipLaunchKernelGGL(init_state, dim3(1), dim3(64), 0, s, st);
   hipLaunchKernelGGL((pad_square<T>), dim3(grid_of((size_t)Tp * Tp)), dim3(256), 0, s, V, R, Tp, Vp);
   hipLaunchKernelGGL((pad_rows<T>), dim3(grid_of((size_t)n * Tp)), dim3(256), 0, s, M, n, R, Tp, Mp);
-  StepProb<T> hp{Vp, ldiag, diagL, Mp, st, nblk, n, flow, cflow, dpart};
+  StepProb<T> hp{Vp, ldiag, diagL, Mp, st, nblk, n, flow, cflow, dpart, bflow};
   if (hipMemcpyAsync(prob, &hp, sizeof(hp), hipMemcpyHostToDevice, s) != hipSuccess) return CPD_ERR_HIP;
   for (int sched : {SCHED_CHOL_FWD, SCHED_BWD}) {
     for (const SolveItem& it : solve_schedule(sched, nblk, pw)) {
@@ -91,7 +92,7 @@ cpd_status solve_impl(int R, int n, const T* V, const T* M, T* F, void* ws, hipS
         std::vector<int> tab = {0, step_tiles(it.mode, nblk, n, it.cfg)};
         int cnt = 1, total = tab[1];
         if (is_flow_mode(it.mode)) {
-          tab = flow_segments(it.mode, {nblk}, {n});
+          tab = flow_segments(it.mode, {nblk}, {n}, {0});
           cnt = (int)tab.size() / 3 - 1;
           total = tab[3 * cnt];
         }

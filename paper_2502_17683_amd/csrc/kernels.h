@@ -51,6 +51,7 @@ struct GemmArgs {
   void* part = nullptr;
   int32_t* cnt = nullptr;
   int32_t vec = 0;
+  int32_t kdiag = 0;   // op(B) is zero above row n0 of column block n0 / 64: K starts there
   int32_t mirror = 0;  // with lower and op(A) = A^T: C is symmetric, and its upper tiles are stored as well
 };
 struct GemmF64 {
@@ -133,6 +134,11 @@ struct StepProb {
   int32_t* cflow;  // ready flags of the dataflow factorisation, nblk^2 + 2 nblk,
                    // then CU_SLOTS per-compute-unit counters
   T* dpart;        // diagonal blocks updated through column k - 2, nblk x 64 x 64
+  int32_t* bflow;  // ready flags of the dataflow backward solve, ceil(n / 64) x nblk
+  // Inverse form (null: off): the forward solve also takes the rows of the
+  // identity, whose solution L^{-T} goes to the upper blocks of E (Tp x Tp,
+  // zero below), and the backward solve F = G L^{-1} is one product.
+  T* E = nullptr;
 };
 // Per-compute-unit counters of the dataflow factorisation (an XCC, shader
 // engine, shader array and CU index from the hardware id registers).
@@ -142,9 +148,9 @@ enum StepMode {
   STEP_FWD = 1,
   STEP_BWD = 2,
   STEP_CHOL_FWD = 3,
-  STEP_FLOW_RESET = 4,     // clears the solve's ready flags (one workgroup per problem)
+  STEP_FLOW_RESET = 4,     // clears the backward solve's ready flags (one workgroup per problem)
   STEP_BWD_FLOW = 5,       // the whole one-level backward solve as one dataflow launch
-  STEP_CFLOW_RESET = 6,    // clears the factorisation's and the solve's ready flags
+  STEP_CFLOW_RESET = 6,    // clears the ready flags of the factorisation and of both solves
   STEP_CHOL_FWD_FLOW = 7,  // one-level factorisation + forward solve as one dataflow launch
   STEP_BWD_PREP = 8,       // per pair of block columns, the products of L the paired solve needs
   STEP_BWD_PAIR = 9        // the one-level backward solve as one dataflow launch, in block pairs
@@ -181,9 +187,11 @@ int step_tiles(int mode, int nblk, int n, StepCfg cfg);
 // from the last column down; per row tile the workgroup of the pair's upper
 // block, then that of its lower block.  The one wait on a higher id is the
 // upper block's wait for the lower block's first action (its right-hand
-// side read), which waits on nothing.  Int triples (first workgroup,
-// problem, column or pair), then (total workgroups, -1, -1).
-std::vector<int> flow_segments(int mode, const std::vector<int>& nblk, const std::vector<int>& n);
+// side read), which waits on nothing.  inv[p]: the problem is in the
+// inverse form.  Int triples (first workgroup, problem, column or pair),
+// then (total workgroups, -1, -1).
+std::vector<int> flow_segments(int mode, const std::vector<int>& nblk, const std::vector<int>& n,
+                               const std::vector<char>& inv);
 inline bool is_flow_mode(int mode) {
   return mode == STEP_CHOL_FWD_FLOW || mode == STEP_BWD_FLOW || mode == STEP_BWD_PAIR;
 }
@@ -195,6 +203,7 @@ int set_flow_spin_limit(int polls);
 // STEP_BWD_PAIR), 1 one block column per hop (STEP_BWD_FLOW); returns the
 // previous value.
 int set_bwd_form(int form);
+int get_bwd_form();
 // Launches one step of `mode`.  offs: nprob + 1 prefix sums of the
 // problems' workgroups, or for a dataflow mode the segment table, with
 // nprob its segment count.
@@ -238,6 +247,8 @@ std::vector<SolveItem> solve_schedule(int sched, int max_nblk, int pw);
 template <typename T>
 struct FormVArgs {
   T* V; const T* g0; const T* g1; const T* g2; DevState* st; int Tp; int R;
+  // the dataflow solve's ready flags, cleared beside V (the first pass only)
+  int32_t *flow, *cflow, *bflow; int nflow, ncflow;
 };
 template <typename T>
 void form_v_group(hipStream_t s, const FormVArgs<T>* tab, int nprob, int max_Tp, int retry_pass);
@@ -247,9 +258,11 @@ void retry_prepare_group(hipStream_t s, const FormVArgs<T>* tab, int nprob, int 
 template <typename T>
 struct NormArgs {
   const T* Msol; T* F; T* lam; const T* Msave; double* inner_part; DevState* st; int n; int R; int ld;
+  int from_F = 0;  // inverse form: the solution is in F already (normalised in place)
 };
+// slow: the problems in the damped-retry pass have theirs in Msol all the same.
 template <typename T>
-void normalise_group(hipStream_t s, const NormArgs<T>* tab, int nprob, int max_R);
+void normalise_group(hipStream_t s, const NormArgs<T>* tab, int nprob, int max_R, int slow);
 // Tied model: <G, G~> partials lam[k] sum_s F3[s,k] M3[s,k] (F3 passed as
 // Msol, M3 as Msave; F unused).
 template <typename T>

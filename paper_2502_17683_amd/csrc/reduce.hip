@@ -16,12 +16,21 @@ namespace thccp {
 // tiles only, which cover them.  One workgroup per lower block (row-major
 // order: block row r holds r + 1 blocks), two adjacent elements per thread
 // and step.
+// The launch's last workgroup of a problem clears the ready flags of the
+// solve that follows (two launches of ~5 us per mode update before).
 template <typename T>
 __global__ __launch_bounds__(256) void form_V_kernel(const FormVArgs<T>* tab, int retry_pass) {
   const FormVArgs<T> a = tab[blockIdx.y];
   DevState* st = a.st;
   if (st->done) return;
   if (retry_pass && !st->retry_active) return;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (retry_pass) return;
+    const gptr<int32_t> f = as_global(a.flow), c = as_global(a.cflow), b = as_global(a.bflow);
+    for (int e = threadIdx.x; e < a.nflow; e += 256) f[e] = b[e] = 0;
+    for (int e = threadIdx.x; e < a.ncflow; e += 256) c[e] = 0;
+    return;
+  }
   const int nb = a.Tp / 64, b = blockIdx.x;
   if (b >= nb * (nb + 1) / 2) return;
   int r = (int)((sqrtf(8.f * (float)b + 1.f) - 1.f) * 0.5f);
@@ -65,7 +74,7 @@ __global__ __launch_bounds__(256) void form_V_kernel(const FormVArgs<T>* tab, in
 template <typename T>
 void form_v_group(hipStream_t s, const FormVArgs<T>* tab, int nprob, int max_Tp, int retry_pass) {
   const int nb = max_Tp / 64;
-  hipLaunchKernelGGL((form_V_kernel<T>), dim3(nb * (nb + 1) / 2, nprob), dim3(256), 0, s, tab, retry_pass);
+  hipLaunchKernelGGL((form_V_kernel<T>), dim3(nb * (nb + 1) / 2 + 1, nprob), dim3(256), 0, s, tab, retry_pass);
 }
 
 // After the first factorisation pass: arm the damped retry (mu = 1e-12
@@ -115,7 +124,7 @@ void retry_prepare_group(hipStream_t s, const FormVArgs<T>* tab, int nprob, int 
 // they are summed (in row order), so that each thread has 16 loads in
 // flight instead of waiting on one load per row.
 template <typename T>
-__global__ __launch_bounds__(256) void normalise_kernel(const NormArgs<T>* tab) {
+__global__ __launch_bounds__(256) void normalise_kernel(const NormArgs<T>* tab, int slow) {
   __shared__ double ss[16][16];
   __shared__ double si[16][16];
   const NormArgs<T> a = tab[blockIdx.y];
@@ -124,7 +133,8 @@ __global__ __launch_bounds__(256) void normalise_kernel(const NormArgs<T>* tab) 
   const int col = blockIdx.x * 16 + c;
   if (blockIdx.x * 16 >= a.R) return;
   const int n = a.n, R = a.R, ld = a.ld;
-  const gptr<const T> Msol = as_global(a.Msol), Msave = as_global(a.Msave);
+  const gptr<const T> Msol = as_global(a.from_F && !(slow && a.st->retry_active) ? (const T*)a.F : a.Msol);
+  const gptr<const T> Msave = as_global(a.Msave);
   constexpr int NB = 16;
   double x = 0.0, y = 0.0;
   if (col < R) {
@@ -177,8 +187,8 @@ __global__ __launch_bounds__(256) void normalise_kernel(const NormArgs<T>* tab) 
 }
 
 template <typename T>
-void normalise_group(hipStream_t s, const NormArgs<T>* tab, int nprob, int max_R) {
-  hipLaunchKernelGGL((normalise_kernel<T>), dim3((max_R + 15) / 16, nprob), dim3(256), 0, s, tab);
+void normalise_group(hipStream_t s, const NormArgs<T>* tab, int nprob, int max_R, int slow) {
+  hipLaunchKernelGGL((normalise_kernel<T>), dim3((max_R + 15) / 16, nprob), dim3(256), 0, s, tab, slow);
 }
 
 // Tied model: inner_part[k] = lam[k] sum_s F3[s,k] M3[s,k] (the <G, G~>
@@ -618,8 +628,8 @@ template void form_v_group<double>(hipStream_t, const FormVArgs<double>*, int, i
 template void form_v_group<float>(hipStream_t, const FormVArgs<float>*, int, int, int);
 template void retry_prepare_group<double>(hipStream_t, const FormVArgs<double>*, int, int);
 template void retry_prepare_group<float>(hipStream_t, const FormVArgs<float>*, int, int);
-template void normalise_group<double>(hipStream_t, const NormArgs<double>*, int, int);
-template void normalise_group<float>(hipStream_t, const NormArgs<float>*, int, int);
+template void normalise_group<double>(hipStream_t, const NormArgs<double>*, int, int, int);
+template void normalise_group<float>(hipStream_t, const NormArgs<float>*, int, int, int);
 template void fit_group<double>(hipStream_t, const FitArgs<double>*, int, int, int, double, double, int, double,
                                 int);
 template void fit_group<float>(hipStream_t, const FitArgs<float>*, int, int, int, double, double, int, double,

@@ -72,3 +72,29 @@ def test_inference_row_tiles(rows):
     out = net.infer_bf16(x)
     part = torch.cat([net.infer_bf16(x[a:a + 5000].contiguous()) for a in range(0, rows, 5000)])
     assert torch.equal(out, part) and bool(torch.isfinite(out).all())
+
+
+@pytest.mark.parametrize("r_cp", [1, 64, 65, 640, 641])
+def test_backward_solve_forms_of_a_plan(r_cp):
+    """One FP64 sweep with the backward solve as one product (up to ten block
+    columns) and in block pairs (a plan with panels as wide as the matrix
+    keeps them): both within the solve's rounding of each other, the
+    asynchronous sweep bit for bit the synchronised one."""
+    from paper_2502_17683_amd import CPD
+    from synth import init_factors, make_thc
+    n, r_thc = 45, 260
+    X, Z = make_thc(n, r_thc, r_cp)
+    init = [to_dev(f) for f in init_factors([n] * 4, r_cp, 1000 + r_cp)]
+    got = []
+    for panel, sync in ((0, True), (0, False), (64, True)):
+        plan = CPD(to_dev(X), to_dev(Z), r_cp, init, tol=0.0, fit_floor=0.0, solve_panel=panel)
+        plan.sweep(1, sync=sync)
+        F, lam = plan.factors()
+        got.append(F + [lam])
+        cond = plan.stats()["cond_est"]
+        plan.close()
+    for a, b, c in zip(*got):
+        assert torch.equal(a, b)
+        # four updates, each a solve with a normal matrix of this condition
+        err = float((a - c).norm() / c.norm())
+        assert err <= 200 * r_cp * max(cond, 1.0) * 2.0 ** -53, (err, cond)

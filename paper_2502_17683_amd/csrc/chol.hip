@@ -24,7 +24,8 @@
 // The sequential parts keep a 64 x 64 tile in registers.  The diagonal
 // factorisation uses the "strip" layout (thread t owns row t / 4 and the
 // 16 columns (t % 4) + 4u, so the four threads of a row hold one 4-column
-// block) and publishes four columns per barrier.  The solve of a panel tile
+// block) and publishes four columns per barrier; the dataflow factorisation
+// of FP64 plans takes 16-column panels instead (panel_potrf).  The solve of a panel tile
 // with L_kk uses the "block-4" layout (4 rows x 4 columns per thread, the
 // solved value broadcast inside a 16-lane DPP row), which needs a quarter
 // of the strip layout's LDS reads.
@@ -158,26 +159,6 @@ __device__ __forceinline__ void b4_bwd(T s[16], const T* L, const T* invd, int j
   B4Solve<T, false, TB - 1>::run(s, L, invd, j, ic, lk);
 }
 
-// Cholesky of the 64 x 64 block held in strip layout d (lower part used),
-// four columns per barrier.  Column block b (columns 4b .. 4b+3) is exactly
-// register d[b] of the four threads of a row (column offset q0).  Per
-// block: every thread publishes d[b] = A[r][4b+q0] (updated by all earlier
-// blocks) to cb[b & 1][r][q0] (row-major, so a row's four values are one
-// 32-byte read); one barrier (the two buffers alternate); every thread then
-// factors the 4 x 4 diagonal block D = Ld Ld^T from cb (redundantly), reads
-// its row a_r = A[r][4b..4b+3] back from cb, forms y = a_r Ld^{-T} (row r of
-// the block column of L) and w = y Ld^{-1} = a_r D^{-1}, and updates its
-// trailing columns k = q0 + 4u, u > b, by d[u] -= w . A[k][4b..4b+3] (four
-// fused multiply-adds, in the order of the four columns), the reads of
-// A[k][.] running two columns ahead of the updates.  On return L is in LDS
-// (row-major, stride LDT, zero above the diagonal) and invd[c] =
-// 1 / L[c][c].  Returns false if a pivot was not positive (the factor is
-// then finite garbage).
-// PANEL: the thread also carries row r of a tile below the block in e[16]
-// (same layout, published to cb[2 + (b & 1)]) through every column step,
-// which solves it against L^T; the block's own L is then not kept (the
-// values that the trailing updates use are the published A[k][.], so the
-// tile comes out bitwise as it would beside the full factorisation).
 // Keeps a value's computation at this point of the instruction stream (an
 // empty asm statement that reads and writes it; such statements keep their
 // source order).
@@ -224,10 +205,11 @@ template <typename T>
 struct PivotRsqrt {
   T x, y, t, e, p, qv;
   bool bad;
-  __device__ __forceinline__ void s0(T xin, bool& ok) {
+  template <typename F>
+  __device__ __forceinline__ void s0(T xin, F& ok) {
     x = xin;
     bad = !(x > T(0)) || !__builtin_isfinite(x);
-    if (bad) ok = false;
+    if (bad) ok = F(0);
     if constexpr (sizeof(T) == 8) y = __builtin_amdgcn_rsq(x);
     else y = T(1) / sqrtf(x);
     pin(y);
@@ -542,6 +524,162 @@ __device__ __forceinline__ bool strip_potrf4_panel(T d[16], T e[16], T* invd, T*
   const T z[4] = {T(0), T(0), T(0), T(0)};
   Potrf4<T, 0, true>::run(d, e, cb, invd, r, q0, ok, z, z);
   return ok;
+}
+
+// --------------------------------------------- 16-column panels (FP64)
+// The factorisation of a 64 x 64 block with a 64 x 64 tile below it carried
+// through, from the accumulators that the block's last update leaves: wave w
+// holds rows 16w .. 16w+15 of the block (dd, 16 x 16 tiles dd[tj], tj <= w)
+// and of the tile (acc).  Four panels of 16 columns.  In a panel every lane
+// holds one row of the panel's diagonal block (x; the four 16-lane DPP rows
+// hold the same 16 rows, so every wave factors it alone, and a value of
+// column j travels by row_newbcast from lane k) and one row of the wave's
+// own below it (y: rows of the tile in the even DPP rows, of the block in
+// the odd ones), which is scaled and updated by the same broadcast.  After a
+// panel the columns right of it take one rank-16 update on the matrix
+// cores.  Bound by the issue of a panel's ~600 FP64 instructions per wave (5
+// cycles each; they share the unit with the matrix instructions, so nothing
+// hides them): 20.7k cycles a block, 11.6k of them in the four panels'
+// columns, against 23.0k of the strip form; the diagonal workgroup, whose
+// X_k = L_kk^{-double} rides along, saves its separate substitution besides.
+// N = 100, R_cp = 400, four sweeps: 3.13 -> 2.80 ms; (41, 203), R_cp = 491,
+// two sweeps: 1.96 -> 1.78 ms; N = 20: 967 -> 855 us.
+__device__ double dpp_f64(double old, double v, int ctrl, int row_mask, int bank_mask, bool bound)
+    __asm("llvm.amdgcn.update.dpp.f64");
+template <int N>
+__device__ __forceinline__ double rnb64(double v) {
+  return dpp_f64(v, v, 0x150 + N, 0xF, 0xF, true);  // one 64-bit move (rnb: two of 32 bits)
+}
+// Row strides in LDS, in doubles: of a 16 x 16 tile, and of the solved
+// 64 x 64 tile (16-byte reads of sixteen rows in distinct groups of four
+// banks).
+constexpr int PLD = 18, LDO = 66;
+constexpr int PTILE = 16 * PLD;
+__device__ __forceinline__ void row16_load(double x[16], const double* p) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const double2 u = ((const double2*)p)[c];
+    x[2 * c] = u.x;
+    x[2 * c + 1] = u.y;
+  }
+}
+__device__ __forceinline__ void row16_store(const double x[16], double* p) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) ((double2*)p)[c] = double2{x[2 * c], x[2 * c + 1]};
+}
+__device__ __forceinline__ void tile16_store(const d4_t& t, double* p, int lane) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) p[dsub_row<double>(lane, r) * PLD + (lane & 15)] = t[r];
+}
+
+// Columns J .. 15 of a panel, il = 1 / L_JJ: scale, update the next column,
+// and the steps of its pivot with the updates of the columns beyond spread
+// over them.
+template <int J, int K0, int K1>
+__device__ __forceinline__ void panel_update(double x[16], double y[16]) {
+  if constexpr (K0 < K1) {
+    const double l = rnb64<K0>(x[J]);
+    x[K0] = fma_t(-l, x[J], x[K0]);
+    y[K0] = fma_t(-l, y[J], y[K0]);
+    pin(x[K0]);
+    pin(y[K0]);
+    panel_update<J, K0 + 1, K1>(x, y);
+  }
+}
+template <int J>
+__device__ __forceinline__ void panel_cols(double x[16], double y[16], double il, int& ok) {
+  x[J] *= il;
+  pin(x[J]);
+  y[J] *= il;
+  pin(y[J]);
+  if constexpr (J < 15) {
+    constexpr int K = J + 2, N = 14 - J;
+    panel_update<J, J + 1, J + 2>(x, y);
+    PivotRsqrt<double> pv;
+    pv.s0(rnb64<J + 1>(x[J + 1]), ok);
+    pin(ok);  // (one flag: the masks of sixteen pivots spill)
+    panel_update<J, K, K + N * 2 / 6>(x, y);
+    pv.s1();
+    panel_update<J, K + N * 2 / 6, K + N * 3 / 6>(x, y);
+    pv.s2();
+    panel_update<J, K + N * 3 / 6, K + N * 4 / 6>(x, y);
+    pv.s3();
+    panel_update<J, K + N * 4 / 6, K + N * 5 / 6>(x, y);
+    const double iln = pv.s4();
+    panel_update<J, K + N * 5 / 6, K + N>(x, y);
+    panel_cols<J + 1>(x, y, iln, ok);
+  }
+}
+
+// Panels P .. 3.  D: 2 x 4 tiles (of the block's rows, the panels in turn),
+// E: 4 tiles (of the tile's rows); out: the solved tile, row stride LDO.
+// diag (or null): gets L_cc.
+template <int P>
+__device__ __forceinline__ void panels(d4_t dd[4], d4_t acc[4], double* D, double* E, double* out,
+                                       double* diag, int& ok, int lane, int w) {
+  const int g = lane >> 4, i = lane & 15;
+  double* const Dp = D + (P & 1) * 4 * PTILE;
+  if constexpr (P == 0) {
+    tile16_store(dd[0], Dp + w * PTILE, lane);
+    tile16_store(acc[0], E + w * PTILE, lane);
+  }
+  __syncthreads();
+  const bool below = (g & 1) && w > P;
+  double x[16], y[16];
+  row16_load(x, Dp + P * PTILE + i * PLD);
+  row16_load(y, (below ? Dp : E) + w * PTILE + i * PLD);
+  PivotRsqrt<double> pv;
+  pv.s0(rnb64<0>(x[0]), ok);
+  pv.s1();
+  pv.s2();
+  pv.s3();
+  panel_cols<0>(x, y, pv.s4(), ok);
+  double* const orow = out + (16 * w + i) * LDO + 16 * P;
+  if (g == 0) row16_store(y, orow);
+  if (diag && w == P) {
+    double d = x[0];
+#pragma unroll
+    for (int c = 1; c < 16; ++c) {
+      int ic = i;  // (a fresh compare each: sixteen kept masks spill)
+      pin(ic);
+      d = ic == c ? x[c] : d;
+    }
+    diag[16 * P + i] = d;
+  }
+  if constexpr (P < 3) {
+    if (below && g == 1) row16_store(y, Dp + w * PTILE + i * PLD);
+    __syncthreads();
+    double a[4], b[4], l[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      a[s] = -orow[4 * s + g];
+      b[s] = -Dp[w * PTILE + i * PLD + 4 * s + g];
+    }
+#pragma unroll
+    for (int tj = P + 1; tj < 4; ++tj) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) l[s] = Dp[tj * PTILE + i * PLD + 4 * s + g];
+      if (tj <= w) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) dd[tj] = mfma4(b[s], l[s], dd[tj]);
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[tj] = mfma4(a[s], l[s], acc[tj]);
+    }
+    tile16_store(dd[P + 1], D + (((P + 1) & 1) * 4 + w) * PTILE, lane);
+    tile16_store(acc[P + 1], E + w * PTILE, lane);
+    panels<P + 1>(dd, acc, D, E, out, diag, ok, lane, w);
+  }
+}
+// dd: the block (its lower 16 x 16 tiles); acc: the tile; lds: 12 PTILE
+// elements; out: on return (before a barrier) the tile solved against L^T.
+// Returns false if a pivot was not positive (the factor is then finite
+// garbage).
+__device__ __forceinline__ bool panel_potrf(d4_t dd[4], d4_t acc[4], double* lds, double* out,
+                                            double* diag, int lane, int w) {
+  int ok = 1;
+  panels<0>(dd, acc, lds, lds + 8 * PTILE, out, diag, ok, lane, w);
+  return ok != 0;
 }
 
 // ------------------------------------------------------- layout transfers
@@ -1042,9 +1180,10 @@ __device__ __forceinline__ void put_block2(T* S, const T v[16], int tid) {
     put_block<T, TRANSPOSE>(S, v, tid);
   }
 }
-// A 64-column tile held in LDS (row-major, stride LDT) stored through
+// A 64-column tile held in LDS (row-major, stride LD) stored through
 // device-coherent 16-byte stores, in the pair layout of fetch_block2_coherent
 // (rows at or past nrows are dropped by the buffer's bound).  FP64 only.
+template <int LD = LDT>
 __device__ __forceinline__ void store_block2_coherent(const double* S, double* g, size_t ld, int nrows, int tid) {
   typedef unsigned int u4 __attribute__((ext_vector_type(4)));
   constexpr int SC1 = 16;  // cache policy: device-coherent, as the agent-scope stores
@@ -1053,8 +1192,8 @@ __device__ __forceinline__ void store_block2_coherent(const double* S, double* g
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int pr = tid + 256 * e, r = pr >> 5, c = 2 * (pr & 31);
-    const unsigned long long x0 = __builtin_bit_cast(unsigned long long, S[r * LDT + c]);
-    const unsigned long long x1 = __builtin_bit_cast(unsigned long long, S[r * LDT + c + 1]);
+    const unsigned long long x0 = __builtin_bit_cast(unsigned long long, S[r * LD + c]);
+    const unsigned long long x1 = __builtin_bit_cast(unsigned long long, S[r * LD + c + 1]);
     const u4 v = {(unsigned)x0, (unsigned)(x0 >> 32), (unsigned)x1, (unsigned)(x1 >> 32)};
     __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)((r * ld + c) * sizeof(double)), 0, SC1);
   }
@@ -1536,13 +1675,17 @@ __device__ __forceinline__ void lower_llt(typename Acc4<T>::type q[4], typename 
   }
 }
 
-template <typename T>
+// STRIP: the diagonal blocks by strip_potrf4 (FP32 plans, and the FP64 solves
+// of split-BF16 plans: their low-precision products carry a last bit on, so
+// they keep its rounding); otherwise (FP64 plans) by panel_potrf.
+template <typename T, bool STRIP>
 __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>* probs, const int* seg,
                                                                int nseg, int spin_limit) {
   typedef typename Acc4<T>::type acc_t;
-  __shared__ T S0[TB * LDT];
-  __shared__ T S1[TB * LDT];
-  __shared__ __attribute__((aligned(16))) T colbuf[20 * TB];  // 3 published column blocks, 2 tile blocks
+  __shared__ __attribute__((aligned(16))) T S0[TB * (STRIP ? LDT : LDO)];
+  __shared__ __attribute__((aligned(16))) T S1[TB * LDT];
+  // 3 published column blocks, 2 tile blocks (strip form); a 16 x 16 tile
+  __shared__ __attribute__((aligned(16))) T colbuf[(STRIP ? 20 : 4) * TB];
   __shared__ T invd[TB];
   __shared__ int stalled;
   int pid, k, bid;
@@ -1685,52 +1828,74 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
 #pragma unroll
       for (int r = 0; r < 4; ++r) dd[0][r] -= colbuf[lane * 4 + r];
     }
-    acc_to_lds<T>(dd, S1, lane, w);
-    if (!diag) acc_to_lds<T>(acc, S0, lane, w);
-    __syncthreads();
-    T d[16];
-    lds_to_strip<T>(S1, d, sr, q0);
-    if constexpr (sizeof(T) == 8) {
-      if (!diag) {
-        // the tile's rows ride through the factorisation of D_k: L_ik comes
-        // out of the same column steps, with no separate substitution
-        // (FP64 only: the FP32 instance spills with the second strip)
-        T e[16];
-        lds_to_strip<T>(S0, e, sr, q0);
-        strip_potrf4_panel<T>(d, e, invd, colbuf, sr, q0);
-        // L_ik through LDS (S0 is free: every thread read its strip before
-        // the factorisation's first barrier) into coalesced 16-byte stores
+    if constexpr (!STRIP) {
+      // the tile's rows, or those of the identity (X_k = L_kk^{-T}, for the
+      // forward solve), ride through the factorisation of D_k
+      if (diag) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) S0[sr * LDT + q0 + 4 * u] = e[u];
-        __syncthreads();
-        store_block2_coherent(S0, tile, Tp, TB, tid);
+        for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[tj][r] = acc_row<T>(lane, w, r) == acc_col(lane, tj) ? T(1) : T(0);
+      }
+      const bool ok = panel_potrf(dd, acc, S1, S0, diag ? invd : nullptr, lane, wu);
+      __syncthreads();
+      if (diag) {
+        if (!ok && tid == 0) atomicExch(&st->chol_fail, 1);
+        if (tid < TB) as_global(q.diagL)[k * TB + tid] = invd[tid];
+        store_block2_coherent<LDO>(S0, q.ldiag + (size_t)k * TB * TB, TB, TB, tid);
+        if (q.E) store_block2_coherent<LDO>(S0, q.E + (size_t)k * TB * Tp + (size_t)k * TB, Tp, TB, tid);
+        publish(xfl + k);
+      } else {
+        store_block2_coherent<LDO>(S0, tile, Tp, TB, tid);
+        publish(lfl + i * nblk + k);
+        if (k >= 1) chain_end();
+      }
+    } else {
+      acc_to_lds<T>(dd, S1, lane, w);
+      if (!diag) acc_to_lds<T>(acc, S0, lane, w);
+      __syncthreads();
+      T d[16], s[16];
+      lds_to_strip<T>(S1, d, sr, q0);
+      if constexpr (sizeof(T) == 8) {
+        if (!diag) {
+          // the tile's rows ride through the factorisation of D_k: L_ik comes
+          // out of the same column steps, with no separate substitution
+          // (FP64 only: the FP32 instance spills with the second strip)
+          T e[16];
+          lds_to_strip<T>(S0, e, sr, q0);
+          strip_potrf4_panel<T>(d, e, invd, colbuf, sr, q0);
+          // L_ik through LDS (S0 is free: every thread read its strip before
+          // the factorisation's first barrier) into coalesced 16-byte stores
+#pragma unroll
+          for (int u = 0; u < 16; ++u) S0[sr * LDT + q0 + 4 * u] = e[u];
+          __syncthreads();
+          store_block2_coherent(S0, tile, Tp, TB, tid);
+          publish(lfl + i * nblk + k);
+          if (k >= 1) chain_end();
+          return;
+        }
+      }
+      __syncthreads();
+      const bool ok = strip_potrf4<T>(d, S1, invd, colbuf, sr, q0);  // S1 = L_kk
+      if (!diag) {  // FP32: the tile by substitution with L_kk
+        lds_to_b4<T>(S0, s, bg, bj);
+        b4_fwd<T>(s, S1, invd, bj);
+        store_b4_coherent<T>(s, tile, Tp, bg, bj);
         publish(lfl + i * nblk + k);
         if (k >= 1) chain_end();
         return;
       }
-    }
-    __syncthreads();
-    const bool ok = strip_potrf4<T>(d, S1, invd, colbuf, sr, q0);  // S1 = L_kk
-    T s[16];
-    if (!diag) {  // FP32: the tile by substitution with L_kk
-      lds_to_b4<T>(S0, s, bg, bj);
-      b4_fwd<T>(s, S1, invd, bj);
-      store_b4_coherent<T>(s, tile, Tp, bg, bj);
-      publish(lfl + i * nblk + k);
-      if (k >= 1) chain_end();
-      return;
-    }
-    // the diagonal workgroup: L_kk, and X_k = L_kk^{-T} for the forward solve
-    if (!ok && tid == 0) atomicExch(&st->chol_fail, 1);
-    if (tid < TB) as_global(q.diagL)[k * TB + tid] = S1[tid * LDT + tid];
+      // the diagonal workgroup: L_kk, and X_k = L_kk^{-T} for the forward solve
+      if (!ok && tid == 0) atomicExch(&st->chol_fail, 1);
+      if (tid < TB) as_global(q.diagL)[k * TB + tid] = S1[tid * LDT + tid];
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
+      for (int ii = 0; ii < 4; ++ii)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) s[4 * ii + v] = (4 * bg + ii == bj + 16 * v) ? T(1) : T(0);
-    b4_fwd<T>(s, S1, invd, bj);  // X_k
-    store_b4_coherent<T>(s, q.ldiag + (size_t)k * TB * TB, TB, bg, bj);
-    if (q.E) store_b4_coherent<T>(s, q.E + (size_t)k * TB * Tp + (size_t)k * TB, Tp, bg, bj);
-    publish(xfl + k);
+        for (int v = 0; v < 4; ++v) s[4 * ii + v] = (4 * bg + ii == bj + 16 * v) ? T(1) : T(0);
+      b4_fwd<T>(s, S1, invd, bj);  // X_k
+      store_b4_coherent<T>(s, q.ldiag + (size_t)k * TB * TB, TB, bg, bj);
+      publish(xfl + k);
+    }
     return;
   }
 
@@ -1855,7 +2020,14 @@ void step_group(hipStream_t s, int mode, const StepProb<T>* probs, const int* of
       hipLaunchKernelGGL((cflow_reset_kernel<T>), dim3(nprob), block, 0, s, probs);
       break;
     case STEP_CHOL_FWD_FLOW:  // offs: segment table, nprob: its segment count
-      hipLaunchKernelGGL((chol_fwd_flow_kernel<T>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit);
+      if constexpr (sizeof(T) == 8) {
+        if (!cfg.strip) {
+          hipLaunchKernelGGL((chol_fwd_flow_kernel<T, false>), grid, block, 0, s, probs, offs, nprob,
+                             g_flow_spin_limit);
+          break;
+        }
+      }
+      hipLaunchKernelGGL((chol_fwd_flow_kernel<T, true>), grid, block, 0, s, probs, offs, nprob, g_flow_spin_limit);
       break;
     case STEP_BWD_PREP:
       hipLaunchKernelGGL((bwd_prep_kernel<T>), grid, block, 0, s, probs, offs, nprob, retry_pass);

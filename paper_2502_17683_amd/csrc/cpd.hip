@@ -610,12 +610,14 @@ const int partner_of[4] = {1, 0, 3, 2};
 // whose factorisation failed, 2 only problems in the damped-retry pass.
 template <typename T>
 std::vector<SolveLaunch> build_sched(TableBuilder& tb, int sched, int max_nblk, int pw,
-                                     const std::vector<StepProb<T>>& sp, int gate_kind, const std::string& kind) {
+                                     const std::vector<StepProb<T>>& sp, int gate_kind, const std::string& kind,
+                                     bool strip = false) {
   std::vector<SolveLaunch> out;
   for (const SolveItem& it : solve_schedule(sched, max_nblk, pw)) {
     SolveLaunch L;
     L.mode = it.mode;
     L.cfg = it.cfg;
+    L.cfg.strip = strip;
     if (it.mode >= 0 && is_flow_mode(it.mode)) {
       std::vector<int> nb, nr;
       for (auto& q : sp) {
@@ -744,7 +746,7 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
     so.probs = tb.put(sp);
     const int pw = p->panel_width > 0 ? p->panel_width : p->maxNblk;
     so.chol_retry = build_sched<T>(tb, SCHED_CHOL, p->maxNblk, pw, sp, 2, kind);
-    so.cholfwd = build_sched<T>(tb, SCHED_CHOL_FWD, p->maxNblk, pw, sp, 1, kind);
+    so.cholfwd = build_sched<T>(tb, SCHED_CHOL_FWD, p->maxNblk, pw, sp, 1, kind, p->prec == CPD_MIXED_BF16);
     so.bwd = build_sched<T>(tb, SCHED_BWD, p->maxNblk, pw, sp, 0, kind);
     so.binv = gemm_op<T>(tb, binv, false, true, kind + "binv", false);
     so.binv_slow = gemm_op<T>(tb, binv_slow, false, true, kind + "binv", false);

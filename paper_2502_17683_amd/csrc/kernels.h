@@ -173,6 +173,7 @@ struct StepCfg {
   int pw;
   int pc, tc;
   int pf, tf;
+  int strip = 0;  // STEP_CHOL_FWD_FLOW in FP64: diagonal blocks by the strip factorisation
 };
 inline int panel_count(int nblk, int pw) { return (nblk + pw - 1) / pw; }
 // Workgroups of problem (nblk, n) in a launch of `mode` with `cfg`.

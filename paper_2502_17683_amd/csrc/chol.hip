@@ -715,6 +715,35 @@ __device__ __forceinline__ void load_acc(typename Acc4<T>::type acc[4], const T*
       acc[tj][r] = row < nrows ? g[(size_t)row * ld + acc_col(lane, tj)] : T(0);
     }
 }
+// V_ik of the dataflow factorisation, from V or as the Hadamard product of
+// the Grams with the identity on the padding: bitwise what form_v_group
+// writes, without its launch and its pass over V (4 us of a mode update at
+// N = 20, 54 us at R_cp = 4000).  N = 20, four sweeps: 860 -> 803 us; N =
+// 100: 2.80 -> 2.76 ms; N = 800, one sweep: 18.01 -> 17.86 ms.
+template <typename T>
+__device__ __forceinline__ void load_v(typename Acc4<T>::type acc[4], const StepProb<T>& q, int i, int k, int Tp,
+                                       int lane, int w) {
+  const size_t o = (size_t)i * TB * Tp + (size_t)k * TB;
+  if (!q.g0) {
+    load_acc<T>(acc, q.V + o, Tp, TB, lane, w);
+    return;
+  }
+  typename Acc4<T>::type b[4], c[4];
+  load_acc<T>(acc, q.g0 + o, Tp, TB, lane, w);
+  load_acc<T>(b, q.g1 + o, Tp, TB, lane, w);
+  load_acc<T>(c, q.g2 + o, Tp, TB, lane, w);
+#pragma unroll
+  for (int tj = 0; tj < 4; ++tj) acc[tj] = acc[tj] * b[tj] * c[tj];
+  if ((i + 1) * TB > q.R) {  // (i >= k: the tile of the last rows, or none)
+#pragma unroll
+    for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = i * TB + acc_row<T>(lane, w, r), col = k * TB + acc_col(lane, tj);
+        if (row >= q.R || col >= q.R) acc[tj][r] = row == col ? T(1) : T(0);
+      }
+  }
+}
 template <typename T>
 __device__ __forceinline__ void store_acc(const typename Acc4<T>::type acc[4], T* g_, size_t ld, int nrows,
                                           int lane, int w) {
@@ -1757,7 +1786,7 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
     const int i = k + bid;
     const bool diag = i == k;
     T* const tile = blk(i, k);
-    load_acc<T>(acc, tile, Tp, TB, lane, w);  // A_ik, written before the launch
+    load_v<T>(acc, q, i, k, Tp, lane, w);  // A_ik
 #pragma unroll
     for (int tj = 0; tj < 4; ++tj) p[tj] = acc_t{0, 0, 0, 0};
     for (int j = 0; j + 1 < k; ++j) {  // columns j <= k - 2
@@ -1783,7 +1812,7 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
       if (!wait(dfl + k, nullptr)) return;
       load_acc_coherent<T>(dd, q.dpart + (size_t)k * TB * TB, TB, lane, w);
     } else {
-      load_acc<T>(dd, blk(k, k), Tp, TB, lane, w);  // A_kk: no earlier columns to apply
+      load_v<T>(dd, q, k, k, Tp, lane, w);  // A_kk: no earlier columns to apply
     }
     if (k >= 1) {
       // column k - 1: the own tile and D_k

@@ -719,7 +719,12 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
             v->back().want = 1;
           }
       }
-      sp.push_back({b.V, b.ldiag, b.diagL, b.Msol, q.st, q.nblk, q.n[n], b.flow, b.cflow, b.dpart, b.bflow, b.E});
+      const T* g[3];
+      int c = 0;
+      for (int m = 0; m < 4; ++m)
+        if (m != n) g[c++] = b.G[m];
+      sp.push_back({b.V, b.ldiag, b.diagL, b.Msol, q.st, q.nblk, q.n[n], b.flow, b.cflow, b.dpart, b.bflow, b.E,
+                    g[0], g[1], g[2], Rc});
       if (q.inv) {
         GemmArgs<T> g{q.n[n], Rc, Tp, b.Msol, Tp, b.E, nullptr, Tp, b.F[n], Tp, nullptr, T(1), T(0), done};
         g.kdiag = 1;
@@ -727,13 +732,9 @@ void build_typed(TableBuilder& tb, cpd_plan_s* p, Bufs<T> Prob::*bufs, bool gate
         g.gate = &q.st->retry_active;
         binv_slow.push_back(g);
       }
-      const T* g[3];
-      int c = 0;
-      for (int m = 0; m < 4; ++m)
-        if (m != n) g[c++] = b.G[m];
-      fv.push_back({b.V, g[0], g[1], g[2], q.st, Tp, Rc, b.flow, b.cflow, b.bflow, (q.n[n] + 63) / 64 * q.nblk,
-                    (q.nblk + 2) * q.nblk + CU_SLOTS});
-      nm.push_back({b.Msol, b.F[n], b.lam, nullptr, nullptr, q.st, q.n[n], Rc, Tp, q.inv});
+      const FlowFlags flags{b.flow, b.cflow, b.bflow, (q.n[n] + 63) / 64 * q.nblk, (q.nblk + 2) * q.nblk + CU_SLOTS};
+      fv.push_back({b.V, g[0], g[1], g[2], q.st, Tp, Rc, flags});
+      nm.push_back({b.Msol, b.F[n], b.lam, nullptr, nullptr, q.st, q.n[n], Rc, Tp, q.inv, flags});
     }
     if (n == 0 || n == 2) p->core[n] = gemm_op<T>(tb, core, n == 2, false, kind + "core");
     p->back[n] = gemm_op<T>(tb, back, false, false, kind + "back");
@@ -1143,7 +1144,7 @@ void run_sched(cpd_plan_s* p, hipStream_t s, int n, const std::vector<SolveLaunc
                bool resets = false) {
   const StepProb<T>* probs = (const StepProb<T>*)p->steps[n].probs;
   for (const SolveLaunch& L : sched) {
-    // (the launch that forms V has cleared the ready flags)
+    // (the launch that closed the solve before has cleared the ready flags)
     if (!resets && (L.mode == STEP_CFLOW_RESET || L.mode == STEP_FLOW_RESET)) continue;
     if (L.mode < 0) run_gemm<T>(p, s, L.gemm);
     else step_group<T>(s, L.mode, probs, L.offs, L.nseg > 0 ? L.nseg : p->count, L.total, L.cfg, retry_pass);
@@ -1162,7 +1163,8 @@ template <typename T>
 void solve_mode(cpd_plan_s* p, int n, hipStream_t s, bool with_inner, bool fast) {
   const FormVArgs<T>* fv = (const FormVArgs<T>*)p->formv[n];
   StepOps& so = p->steps[n];
-  form_v_group<T>(s, fv, p->count, p->maxTp, 0);
+  // (one level: the factorisation forms V itself)
+  if (so.cholfwd.back().mode != STEP_CHOL_FWD_FLOW) form_v_group<T>(s, fv, p->count, p->maxTp, 0);
   if (fast) {
     run_sched<T>(p, s, n, so.cholfwd, 0);
     run_bwd<T>(p, n, s, false);
@@ -1913,6 +1915,9 @@ cpd_status cpd_kernel_times(cpd_plan p, int32_t reps, double* ms_out) {
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   const bool f32 = p->prec == CPD_FP32;
+  // (the factorisation alone, 5, is not closed by the launch that clears its
+  // flags; the last measurement leaves them clear)
+  const bool forms_v = p->steps[0].cholfwd.back().mode == STEP_CHOL_FWD_FLOW;
   for (int which = 0; which < 8; ++which) {
     auto body = [&]() {
       if (which == 7) {
@@ -1924,12 +1929,12 @@ cpd_status cpd_kernel_times(cpd_plan p, int32_t reps, double* ms_out) {
         // normal-equation solve of mode 0: V, factorisation fused with the
         // forward solve, backward solve, normalisation
         if (f32) {
-          if (which != 6) form_v_group<float>(s, (const FormVArgs<float>*)p->formv[0], p->count, p->maxTp, 0);
+          if (which == 5 || (which == 4 && !forms_v)) form_v_group<float>(s, (const FormVArgs<float>*)p->formv[0], p->count, p->maxTp, 0);
           if (which != 6) run_sched<float>(p, s, 0, p->steps[0].cholfwd, 0);
           if (which != 5) run_bwd<float>(p, 0, s, false, which == 6);
           if (which == 4) normalise_group<float>(s, (const NormArgs<float>*)p->norm[0], p->count, p->maxR, 0);
         } else {
-          if (which != 6) form_v_group<double>(s, (const FormVArgs<double>*)p->formv[0], p->count, p->maxTp, 0);
+          if (which == 5 || (which == 4 && !forms_v)) form_v_group<double>(s, (const FormVArgs<double>*)p->formv[0], p->count, p->maxTp, 0);
           if (which != 6) run_sched<double>(p, s, 0, p->steps[0].cholfwd, 0);
           if (which != 5) run_bwd<double>(p, 0, s, false, which == 6);
           if (which == 4) normalise_group<double>(s, (const NormArgs<double>*)p->norm[0], p->count, p->maxR, 0);

@@ -139,6 +139,10 @@ struct StepProb {
   // identity, whose solution L^{-T} goes to the upper blocks of E (Tp x Tp,
   // zero below), and the backward solve F = G L^{-1} is one product.
   T* E = nullptr;
+  // The Grams whose Hadamard product is V, R x R (null: V is formed already):
+  // the dataflow factorisation multiplies them as it loads its tiles.
+  const T *g0 = nullptr, *g1 = nullptr, *g2 = nullptr;
+  int R = 0;
 };
 // Per-compute-unit counters of the dataflow factorisation (an XCC, shader
 // engine, shader array and CU index from the hardware id registers).
@@ -245,11 +249,16 @@ struct SolveItem {
 std::vector<SolveItem> solve_schedule(int sched, int max_nblk, int pw);
 
 // ------------------------------------------------------------- element-wise
+// The ready flags of a problem's dataflow solves.  Clear before a solve: the
+// launch that closes one (normalise_group) clears them for the next.
+struct FlowFlags {
+  int32_t *flow, *cflow, *bflow;
+  int nflow, ncflow;
+};
 template <typename T>
 struct FormVArgs {
   T* V; const T* g0; const T* g1; const T* g2; DevState* st; int Tp; int R;
-  // the dataflow solve's ready flags, cleared beside V (the first pass only)
-  int32_t *flow, *cflow, *bflow; int nflow, ncflow;
+  FlowFlags flags;  // cleared beside V (the first pass only)
 };
 template <typename T>
 void form_v_group(hipStream_t s, const FormVArgs<T>* tab, int nprob, int max_Tp, int retry_pass);
@@ -260,6 +269,7 @@ template <typename T>
 struct NormArgs {
   const T* Msol; T* F; T* lam; const T* Msave; double* inner_part; DevState* st; int n; int R; int ld;
   int from_F = 0;  // inverse form: the solution is in F already (normalised in place)
+  FlowFlags flags;
 };
 // slow: the problems in the damped-retry pass have theirs in Msol all the same.
 template <typename T>

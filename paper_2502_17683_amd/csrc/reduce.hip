@@ -16,8 +16,14 @@ namespace thccp {
 // tiles only, which cover them.  One workgroup per lower block (row-major
 // order: block row r holds r + 1 blocks), two adjacent elements per thread
 // and step.
-// The launch's last workgroup of a problem clears the ready flags of the
-// solve that follows (two launches of ~5 us per mode update before).
+// The launch's last workgroup of a problem clears its ready flags.  (Sweeps
+// with the dataflow factorisation form V in that launch; this one is for the
+// damped retry and for solves in panels.)
+__device__ __forceinline__ void clear_flags(const FlowFlags& a) {
+  const gptr<int32_t> f = as_global(a.flow), c = as_global(a.cflow), b = as_global(a.bflow);
+  for (int e = threadIdx.x; e < a.nflow; e += 256) f[e] = b[e] = 0;
+  for (int e = threadIdx.x; e < a.ncflow; e += 256) c[e] = 0;
+}
 template <typename T>
 __global__ __launch_bounds__(256) void form_V_kernel(const FormVArgs<T>* tab, int retry_pass) {
   const FormVArgs<T> a = tab[blockIdx.y];
@@ -25,10 +31,7 @@ __global__ __launch_bounds__(256) void form_V_kernel(const FormVArgs<T>* tab, in
   if (st->done) return;
   if (retry_pass && !st->retry_active) return;
   if (blockIdx.x == gridDim.x - 1) {
-    if (retry_pass) return;
-    const gptr<int32_t> f = as_global(a.flow), c = as_global(a.cflow), b = as_global(a.bflow);
-    for (int e = threadIdx.x; e < a.nflow; e += 256) f[e] = b[e] = 0;
-    for (int e = threadIdx.x; e < a.ncflow; e += 256) c[e] = 0;
+    if (!retry_pass) clear_flags(a.flags);
     return;
   }
   const int nb = a.Tp / 64, b = blockIdx.x;
@@ -122,12 +125,18 @@ void retry_prepare_group(hipStream_t s, const FormVArgs<T>* tab, int nprob, int 
 // 16 columns (~R/16 workgroups, enough to keep HBM busy); 16 row groups
 // reduced in a fixed order.  A thread's rows are read 16 at a time before
 // they are summed (in row order), so that each thread has 16 loads in
-// flight instead of waiting on one load per row.
+// flight instead of waiting on one load per row.  The launch's last
+// workgroup of a problem clears the ready flags of its solve, which is over,
+// for the next one (also those of a problem that is done).
 template <typename T>
 __global__ __launch_bounds__(256) void normalise_kernel(const NormArgs<T>* tab, int slow) {
   __shared__ double ss[16][16];
   __shared__ double si[16][16];
   const NormArgs<T> a = tab[blockIdx.y];
+  if (blockIdx.x == gridDim.x - 1) {
+    clear_flags(a.flags);
+    return;
+  }
   if (a.st->done) return;
   const int tid = threadIdx.x, c = tid & 15, g = tid >> 4;
   const int col = blockIdx.x * 16 + c;
@@ -188,7 +197,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(const NormArgs<T>* tab, 
 
 template <typename T>
 void normalise_group(hipStream_t s, const NormArgs<T>* tab, int nprob, int max_R, int slow) {
-  hipLaunchKernelGGL((normalise_kernel<T>), dim3((max_R + 15) / 16, nprob), dim3(256), 0, s, tab, slow);
+  hipLaunchKernelGGL((normalise_kernel<T>), dim3((max_R + 15) / 16 + 1, nprob), dim3(256), 0, s, tab, slow);
 }
 
 // Tied model: inner_part[k] = lam[k] sum_s F3[s,k] M3[s,k] (the <G, G~>

@@ -36,3 +36,31 @@ def test_failed_pivot(c, value):
     V[c, c] = value
     _, failed = test_solve(to_dev(V), torch.ones((3, R), dtype=torch.float64, device="cuda"))
     assert failed
+
+
+@pytest.mark.parametrize("r_cp", [1, 63, 65, 129])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_normal_matrix_formed_by_the_factorisation(r_cp, precision):
+    """One sweep with V formed inside the dataflow factorisation against one
+    with V formed by its own launch (a plan that solves in panels of one
+    block), and the sweep repeated on the same plan (ready flags clear)."""
+    from paper_2502_17683_amd import CPD
+    from synth import init_factors, make_thc
+    say(f"normal matrix r_cp={r_cp} {precision}")
+    n, r_thc = 33, 130
+    X, Z = make_thc(n, r_thc, r_cp)
+    init = [to_dev(f) for f in init_factors([n] * 4, r_cp, 7 + r_cp)]
+    got = []
+    for panel in (0, 1):
+        plan = CPD(to_dev(X), to_dev(Z), r_cp, init, tol=0.0, fit_floor=0.0, solve_panel=panel, precision=precision)
+        for _ in range(2):
+            plan.set_factors(init, torch.ones(r_cp, dtype=torch.float64, device="cuda"))
+            plan.sweep(1)
+            F, lam = plan.factors()
+            got.append([x.double() for x in F + [lam]])
+        cond = plan.stats()["cond_est"]
+        plan.close()
+    u = 2.0 ** -24 if precision == "fp32" else 2.0 ** -53
+    for a, b, c, _ in zip(*got):
+        assert torch.equal(a, b)
+        assert float((a - c).norm() / c.norm()) <= 200 * r_cp * max(cond, 1.0) * u

@@ -1158,6 +1158,10 @@ __device__ __forceinline__ void coherent_store(T* p, T v) {
   typedef typename Bits<T>::type U;
   __hip_atomic_store((gptr<U>)p, __builtin_bit_cast(U, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <typename T>
+struct Vec16 {
+  T v[16 / sizeof(T)];
+};
 // fetch_block / store_acc through device-coherent accesses
 template <typename T>
 __device__ __forceinline__ void fetch_block_coherent(T v[16], const T* g, size_t ld, int nrows, int tid) {
@@ -1167,64 +1171,54 @@ __device__ __forceinline__ void fetch_block_coherent(T v[16], const T* g, size_t
     v[e] = (idx >> 6) < nrows ? coherent_load<T>(g + (size_t)(idx >> 6) * ld + (idx & 63)) : T(0);
   }
 }
-// fetch_block_coherent through device-coherent 16-byte loads (FP64): load e
-// of thread t brings the elements (r, c) and (r, c + 1) of pair p =
-// t + 256 e, r = p / 32, c = 2 (p % 32), into v[2e], v[2e + 1]; rows at or
-// past nrows read zero (the buffer's bound).  put_block2 writes that
-// layout to LDS; other types keep the 8-byte element form.
+// fetch_block_coherent through device-coherent 16-byte loads of N = 16 /
+// sizeof(T) elements: load e of thread t brings the elements (r, c) ..
+// (r, c + N - 1) of chunk p = t + 256 e, r = p / (64 / N), c = N (p % (64 /
+// N)), into v[N e] ..; rows at or past nrows read zero (the buffer's bound).
+// put_block2 writes that layout to LDS.  (FP32 in 4-byte accesses, N = 200,
+// R_cp = 1000, two sweeps: 4.23 ms; so: 4.17.)
 template <typename T>
 __device__ __forceinline__ void fetch_block2_coherent(T v[16], const T* g, size_t ld, int nrows, int tid) {
-  if constexpr (sizeof(T) == 8) {
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    constexpr int SC1 = 16;  // cache policy: device-coherent, as the agent-scope loads
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc((void*)g, (short)0, (int)((size_t)nrows * ld * sizeof(T)), 0x00020000);
+  constexpr int SC1 = 16;  // cache policy: device-coherent, as the agent-scope loads
+  constexpr int N = 16 / sizeof(T), W = TB / N;
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)g, (short)0, (int)((size_t)nrows * ld * sizeof(T)), 0x00020000);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int pr = tid + 256 * e;
-      const u4 x = __builtin_amdgcn_raw_buffer_load_b128(
-          rs, (int)(((pr >> 5) * ld + 2 * (pr & 31)) * sizeof(T)), 0, SC1);
-      v[2 * e] = __builtin_bit_cast(T, (unsigned long long)x.x | ((unsigned long long)x.y << 32));
-      v[2 * e + 1] = __builtin_bit_cast(T, (unsigned long long)x.z | ((unsigned long long)x.w << 32));
-    }
-  } else {
-    fetch_block_coherent<T>(v, g, ld, nrows, tid);
+  for (int e = 0; e < 16 / N; ++e) {
+    const int p = tid + 256 * e;
+    const Vec16<T> x = __builtin_bit_cast(
+        Vec16<T>, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((p / W * ld + N * (p % W)) * sizeof(T)), 0, SC1));
+#pragma unroll
+    for (int h = 0; h < N; ++h) v[N * e + h] = x.v[h];
   }
 }
 template <typename T, bool TRANSPOSE>
 __device__ __forceinline__ void put_block2(T* S, const T v[16], int tid) {
-  if constexpr (sizeof(T) == 8) {
+  constexpr int N = 16 / sizeof(T), W = TB / N;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int pr = tid + 256 * e, r = pr >> 5, c = 2 * (pr & 31);
-      if (TRANSPOSE) {
-        S[c * LDT + r] = v[2 * e];
-        S[(c + 1) * LDT + r] = v[2 * e + 1];
-      } else {
-        S[r * LDT + c] = v[2 * e];
-        S[r * LDT + c + 1] = v[2 * e + 1];
-      }
-    }
-  } else {
-    put_block<T, TRANSPOSE>(S, v, tid);
+  for (int e = 0; e < 16 / N; ++e) {
+    const int p = tid + 256 * e, r = p / W, c = N * (p % W);
+#pragma unroll
+    for (int h = 0; h < N; ++h) S[TRANSPOSE ? (c + h) * LDT + r : r * LDT + c + h] = v[N * e + h];
   }
 }
 // A 64-column tile held in LDS (row-major, stride LD) stored through
-// device-coherent 16-byte stores, in the pair layout of fetch_block2_coherent
-// (rows at or past nrows are dropped by the buffer's bound).  FP64 only.
-template <int LD = LDT>
-__device__ __forceinline__ void store_block2_coherent(const double* S, double* g, size_t ld, int nrows, int tid) {
+// device-coherent 16-byte stores, in the layout of fetch_block2_coherent
+// (rows at or past nrows are dropped by the buffer's bound).
+template <int LD = LDT, typename T>
+__device__ __forceinline__ void store_block2_coherent(const T* S, T* g, size_t ld, int nrows, int tid) {
   typedef unsigned int u4 __attribute__((ext_vector_type(4)));
   constexpr int SC1 = 16;  // cache policy: device-coherent, as the agent-scope stores
+  constexpr int N = 16 / sizeof(T), W = TB / N;
   const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc((void*)g, (short)0, (int)((size_t)nrows * ld * sizeof(double)), 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc((void*)g, (short)0, (int)((size_t)nrows * ld * sizeof(T)), 0x00020000);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int pr = tid + 256 * e, r = pr >> 5, c = 2 * (pr & 31);
-    const unsigned long long x0 = __builtin_bit_cast(unsigned long long, S[r * LD + c]);
-    const unsigned long long x1 = __builtin_bit_cast(unsigned long long, S[r * LD + c + 1]);
-    const u4 v = {(unsigned)x0, (unsigned)(x0 >> 32), (unsigned)x1, (unsigned)(x1 >> 32)};
-    __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)((r * ld + c) * sizeof(double)), 0, SC1);
+  for (int e = 0; e < 16 / N; ++e) {
+    const int p = tid + 256 * e, r = p / W, c = N * (p % W);
+    Vec16<T> x;
+#pragma unroll
+    for (int h = 0; h < N; ++h) x.v[h] = S[r * LD + c + h];
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), rs, (int)((r * ld + c) * sizeof(T)), 0, SC1);
   }
 }
 template <typename T>
@@ -1564,13 +1558,9 @@ __global__ __launch_bounds__(256, 2) void bwd_pair_kernel(const StepProb<T>* pro
   if (!role_a && has_a) {
     // acc_b for the a workgroup, in its tile once its G has been read
     if (!wait_flag(ha, FL_GLOADED)) return;
-    if constexpr (sizeof(T) == 8) {
-      acc_to_lds<T>(acc, S0, lane, w);  // (the wait's barrier: every wave is past its reads of S0)
-      __syncthreads();
-      store_block2_coherent(S0, tile(ha), Tp, nrows, tid);
-    } else {
-      store_acc_coherent<T>(acc, tile(ha), Tp, nrows, lane, w);
-    }
+    acc_to_lds<T>(acc, S0, lane, w);  // (the wait's barrier: every wave is past its reads of S0)
+    __syncthreads();
+    store_block2_coherent(S0, tile(ha), Tp, nrows, tid);
     set_flag(ha, FL_ACCB);
   }
   // f = acc X_k^T
@@ -1620,15 +1610,11 @@ __global__ __launch_bounds__(256, 2) void bwd_pair_kernel(const StepProb<T>* pro
   }
 #pragma unroll
   for (int tj = 0; tj < 4; ++tj) f[tj] = -f[tj];
-  if constexpr (sizeof(T) == 8) {
-    // through LDS into coalesced 16-byte stores
-    __syncthreads();  // every wave is past its reads of S0 / S1
-    acc_to_lds<T>(f, S0, lane, w);
-    __syncthreads();
-    store_block2_coherent(S0, tile(k), Tp, nrows, tid);
-  } else {
-    store_acc_coherent<T>(f, tile(k), Tp, nrows, lane, w);
-  }
+  // through LDS into coalesced 16-byte stores
+  __syncthreads();  // every wave is past its reads of S0 / S1
+  acc_to_lds<T>(f, S0, lane, w);
+  __syncthreads();
+  store_block2_coherent(S0, tile(k), Tp, nrows, tid);
   set_flag(k, FL_F);
 }
 
@@ -1909,7 +1895,13 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
       if (!diag) {  // FP32: the tile by substitution with L_kk
         lds_to_b4<T>(S0, s, bg, bj);
         b4_fwd<T>(s, S1, invd, bj);
-        store_b4_coherent<T>(s, tile, Tp, bg, bj);
+        // (rows 16 w .. 16 w + 15 of S0 are read and written by wave w alone)
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) S0[(4 * bg + ii) * LDT + bj + 16 * v] = s[4 * ii + v];
+        __syncthreads();
+        store_block2_coherent(S0, tile, Tp, TB, tid);
         publish(lfl + i * nblk + k);
         if (k >= 1) chain_end();
         return;
@@ -1966,14 +1958,10 @@ __global__ __launch_bounds__(256, 2) void chol_fwd_flow_kernel(const StepProb<T>
 #pragma unroll
   for (int tj = 0; tj < 4; ++tj) p[tj] = acc_t{0, 0, 0, 0};
   tile_mma64<T>(p, S0, S1, lane, w);  // G_k
-  if constexpr (sizeof(T) == 8) {
-    __syncthreads();  // every wave is past its reads of S0 / S1
-    acc_to_lds<T>(p, S0, lane, w);
-    __syncthreads();
-    store_block2_coherent(S0, tile, Tp, nrows, tid);
-  } else {
-    store_acc_coherent<T>(p, tile, Tp, nrows, lane, w);
-  }
+  __syncthreads();  // every wave is past its reads of S0 / S1
+  acc_to_lds<T>(p, S0, lane, w);
+  __syncthreads();
+  store_block2_coherent(S0, tile, Tp, nrows, tid);
   publish(gfl + k);
 }
 

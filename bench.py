@@ -646,10 +646,10 @@ def bench_exchange(args):
         "useful_tflops": total_flops / (total_ms * 1e-3) / 1e12,
         "per_system": per_system,
         "accuracy_vs_thc_exchange": accuracy,
-        "roofline": {"bound": "mfma", "kernel": "gemm_dma_kernel<false,false,false>: FP64 Z product Y = Z (W2 o W3), largest system",
+        "roofline": {"bound": "mfma", "kernel": "gemm_tile_kernel<double,TileMid,false,false>: FP64 Z product Y = Z (W2 o W3), largest system",
                      "achieved": z_achieved, "peak": MFMA_PEAK["f64"] / 1e12, "unit": "TFLOP/s",
                      "frac": z_achieved * 1e12 / MFMA_PEAK["f64"],
-                     "traffic": measured_traffic("gemm_dma_kernel<false,false,false>",
+                     "traffic": measured_traffic("gemm_tile_kernel<double,TileMid,false,false>",
                                                  "exchange_zproduct_traffic_lt80x400.md"),
                      "avg_launch_us": z_ms * 1e3,
                      "shape": [r_thc, L, r_thc]},

@@ -206,9 +206,9 @@ cpd_status cpd_mttkrp(cpd_plan p, int32_t mode, double* M_dev);
  *       forward triangular solve, backward solve, normalisation),
  *   [5] V + factorisation/forward solve, [6] backward solve,
  *   [7] V alone (the Hadamard product of the Grams).
- *   For a one-level solve (r_cp up to the panel threshold) the
- *   factorisation/forward solve and the backward solve are one dataflow
- *   launch each, after a flag reset.
+ *   For a one-level solve the factorisation forms V itself, and it and the
+ *   backward solve are one dataflow launch each; [5] and [6] also hold the
+ *   launch that clears their ready flags ([5]: that of [7]).
  * Overwrites the plan's intermediate buffers and resets its stopping state:
  * re-initialise the plan before using it again.  Synchronises. */
 cpd_status cpd_kernel_times(cpd_plan p, int32_t reps, double* ms_out);

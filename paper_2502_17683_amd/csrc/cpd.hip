@@ -988,7 +988,8 @@ size_t layout_plan(cpd_plan_s* p, char* base) {
 //     256 517 : 615 us, 400 772 : 937, 640 1068 : 1258, 1000 1705 : 1966; a
 //     batch that fills the chip: 32 x R_cp 400 2063 : 2114, 16 x 640 2427 :
 //     2423, 16 x 768 3209 : 3125, 16 x 960 4786 : 4449.  (The choice may not
-//     look at the batch: a problem gives the same bits alone and in any.)
+//     look at the batch: a problem gives the same bits alone and in any.
+//     Both sides with the strip form of the diagonal blocks.)
 //   - FP64 plans only.  FP32 and split-BF16 plans keep the rounding of the
 //     substitution: their low-precision products carry a last bit on (a
 //     sweep of the Laplace batch moved by 9e-5).

@@ -98,7 +98,7 @@ typedef struct {
   int32_t autotune;       /* 1: time the candidate launch shapes of every
                              grouped product at init and keep the fastest
                              (cached per process by shape): FP64/FP32 tile
-                             edges 64/128; split BF16 128-column tiles of 64
+                             edges 32/64/128; split BF16 128-column tiles of 64
                              or 128 rows, or 128/256 x 256 tiles, the
                              back-projection also with 2 or 4 K slices;
                              0: heuristic                                   */
@@ -501,6 +501,13 @@ int32_t cpd_test_bwd_form(int32_t form);
  *   back-projection and projection; split-K: back-projection); returns the
  *   previous code.  For tests only.  Not thread-safe with plan creation. */
 int32_t cpd_test_split_force(int32_t code);
+/* cpd_test_tile_force: forces the tile edge (32, 64 or 128; any other value:
+ *   off) of the FP64 and FP32 products of plans created afterwards in this
+ *   process and of cpd_test_gemm, except for products split over K past a
+ *   whole number of 64-tiles per compute unit.  The results are the same
+ *   bits in every form.  Returns the previous value.  For tests only.  Not
+ *   thread-safe with plan creation. */
+int32_t cpd_test_tile_force(int32_t bm);
 cpd_status cpd_test_solve(int32_t fp32, int32_t R, int32_t n, const void* V, const void* M, void* F,
                           void* workspace, size_t ws_bytes, void* stream, int32_t* failed, int32_t panel);
 /* cpd_test_gemm_split: C (M x N, FP64) = A B^T from FP64 A (M x K) and

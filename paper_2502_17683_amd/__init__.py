@@ -10,6 +10,7 @@ from .cpd import CPD, CPDBatch, lt_scale_rows, test_gemm, test_solve, test_gemm_
 from .cpd import test_flow_spin_limit  # noqa: F401
 from .cpd import test_bwd_form  # noqa: F401
 from .cpd import test_split_force  # noqa: F401
+from .cpd import test_tile_force  # noqa: F401
 from .lt import (lt_batch_problems, lt_exchange, lt_exchange_workspace_bytes, lt_mp2,  # noqa: F401
                  lt_mp2_workspace_bytes)
 from .warmstart import (WarmStartMLP, ws_features, ws_features_noalloc, ws_select_init, ws_labels, ws_init,  # noqa: F401

@@ -358,6 +358,13 @@ def test_split_force(code):
     return int(_lib.load().cpd_test_split_force(int(code)))
 
 
+def test_tile_force(bm):
+    """Forces the tile edge (32, 64 or 128; 0: off) of the FP64 and FP32
+    products of plans created afterwards and of test_gemm; returns the
+    previous value."""
+    return int(_lib.load().cpd_test_tile_force(int(bm)))
+
+
 def test_solve(V, M, panel=0):
     """F = M V^{-1} through the library's blocked Cholesky and solves
     (panels of `panel` 64-wide blocks; 0: one level)."""

@@ -388,16 +388,37 @@ std::string tune_key(const std::string& kind, const std::vector<int>& dims) {
   return k;
 }
 
+// Tile forms that a launch may run in.  (A split past a whole number of
+// 64-tiles per compute unit is made for 64-tiles.)
+template <typename T>
+std::vector<int> gemm_forms(const std::vector<GemmArgs<T>>& v) {
+  for (auto& g : v)
+    if (g.slices > 1 && g.nfull > 0) return {64};
+  return {32, 64, 128};
+}
+
 // Fills the split and layout fields of the entries for tile form bm and
-// returns the prefix sums of their workgroups.
+// returns the prefix sums of their workgroups.  The room for the partial
+// tiles is that of the form that needs most, so that the size of a workspace
+// and the split of a product follow from the shapes alone, whichever form
+// the tuner has taken or tries.
 template <typename T>
 std::vector<int> gemm_entries(TableBuilder& tb, std::vector<GemmArgs<T>>& v, int bm) {
   size_t bytes = 0;
   int cnts = 0;
-  auto need = [&](const GemmArgs<T>& g) { return g.slices > 1 ? gemm_tile_count(g.M, g.N, bm, g.lower) - g.nfull : 0; };
+  auto need = [](const GemmArgs<T>& g, int f) {
+    return g.slices > 1 ? gemm_tile_count(g.M, g.N, f, g.lower) - g.nfull : 0;
+  };
+  const std::vector<int> forms = gemm_forms(v);
   for (auto& g : v) {
-    bytes += sizeof(T) * (size_t)need(g) * g.slices * bm * bm;
-    cnts += need(g);
+    size_t room = 0;
+    int most = 0;
+    for (int f : forms) {
+      room = std::max(room, sizeof(T) * (size_t)need(g, f) * g.slices * f * f);
+      most = std::max(most, need(g, f));
+    }
+    bytes += room;
+    cnts += most;
   }
   const bool fits = bytes <= tb.part_cap && cnts <= tb.cnt_cap;
   if (fits && bytes > tb.part_need) tb.part_need = bytes;
@@ -407,7 +428,7 @@ std::vector<int> gemm_entries(TableBuilder& tb, std::vector<GemmArgs<T>>& v, int
   int c = 0;
   for (auto& g : v) {
     if (!fits) g.slices = 1;
-    const int t = need(g);
+    const int t = need(g, bm);
     g.part = t ? tb.part + at : nullptr;
     g.cnt = t ? tb.cnt + c : nullptr;
     at += sizeof(T) * (size_t)t * g.slices * bm * bm;
@@ -436,7 +457,7 @@ GroupOp gemm_op(TableBuilder& tb, std::vector<GemmArgs<T>> v, bool at, bool bt, 
   }
   // tile form: autotune cache, else the rule
   op.bm = gemm_tile_form<T>(v);
-  {
+  if (!get_tile_force()) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(tune_key(kind, dims));
     if (it != g_tune.end()) op.bm = it->second;
@@ -1441,8 +1462,8 @@ int rewind_sweep(cpd_plan_s* p) {
   return refresh_all(p, p->stream);
 }
 
-// Tile-size autotuning of the grouped FP64/FP32 GEMMs: times both tile
-// edges of every group once and records the faster in the process cache
+// Tile-size autotuning of the grouped FP64/FP32 GEMMs: times the tile forms
+// of every group once and records the fastest in the process cache
 // (keyed by kind and shapes), which later table builds read.
 template <typename T>
 void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
@@ -1481,10 +1502,7 @@ void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
     }
     float best = 1e30f;
     int best_bm = op.bm;
-    bool tail = false;
-    for (auto& g : host) tail = tail || (g.slices > 1 && g.nfull > 0);
-    for (int bm : {32, 64, 128}) {
-      if (tail && bm != 64) continue;  // (its split is made for 64-tiles)
+    for (int bm : gemm_forms(host)) {
       std::vector<GemmArgs<T>> v(host);
       const std::vector<int> offs = gemm_entries(tb, v, bm);
       if (hipMemcpy(op.tab, v.data(), sizeof(GemmArgs<T>) * v.size(), hipMemcpyHostToDevice) != hipSuccess) return;

@@ -676,6 +676,14 @@ void gemm_plan_slices(GemmArgs<T>& g) {
 template void gemm_plan_slices<double>(GemmArgs<double>&);
 template void gemm_plan_slices<float>(GemmArgs<float>&);
 
+static int g_tile_force = 0;  // host side, tests only: 0 the rule decides
+int set_tile_force(int bm) {
+  const int prev = g_tile_force;
+  g_tile_force = bm == 32 || bm == 64 || bm == 128 ? bm : 0;
+  return prev;
+}
+int get_tile_force() { return g_tile_force; }
+
 // Tile form of a launch.  A split product with unsplit tiles runs in the
 // form its split is made for (64); otherwise the largest form that gives
 // every compute unit work:
@@ -695,6 +703,7 @@ int gemm_tile_form(const std::vector<GemmArgs<T>>& v) {
     split = split || g.slices > 1;
     tail = tail || (g.slices > 1 && g.nfull > 0);
   }
+  if (g_tile_force && !tail) return g_tile_force;
   if (t64 < 256) return 32;
   if (tail || split || t128 < 512) return 64;
   return 4.0 * ((t128 + 255) / 256) / 1.06 < (double)((t64 + 255) / 256) ? 128 : 64;

@@ -151,6 +151,7 @@ size_t cpd_test_solve_workspace(int32_t fp32, int32_t R, int32_t n) {
 }
 
 int32_t cpd_test_flow_spin_limit(int32_t polls) { return set_flow_spin_limit(polls); }
+int32_t cpd_test_tile_force(int32_t bm) { return set_tile_force(bm); }
 int32_t cpd_test_bwd_form(int32_t form) { return set_bwd_form(form); }
 
 cpd_status cpd_test_solve(int32_t fp32, int32_t R, int32_t n, const void* V, const void* M, void* F,

@@ -107,6 +107,11 @@ int gemm_units(const GemmArgs<T>& g, int bm);
 // Tile form (32, 64 or 128) of a grouped launch.
 template <typename T>
 int gemm_tile_form(const std::vector<GemmArgs<T>>& v);
+// Tests: forces the tile form of products prepared afterwards, wherever it
+// is one of the product's own (0: the rule and the autotuner decide);
+// returns the previous value.
+int set_tile_force(int bm);
+int get_tile_force();
 // Grouped launch: tab[nprob] products with identical (a_t, b_t) flags, all
 // of them gemm_tile_ok, in tile form bm; offs[nprob + 1] prefix sums of
 // gemm_units.

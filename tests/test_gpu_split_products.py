@@ -1,0 +1,52 @@
+"""Products of a plan that are split over K give the same bits in every tile
+form, in a tuned plan and its successor, alone and in a batch of any size."""
+import ctypes
+
+import pytest
+import torch
+
+from gpu_util import need_gpu, say, to_dev
+from synth import init_factors, make_thc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    need_gpu()
+
+
+def _run(X, Z, r_cp, init, **kw):
+    from paper_2502_17683_amd import CPD
+    plan = CPD(X, Z, r_cp, init, tol=0.0, fit_floor=0.0, **kw)
+    fits = plan.sweep(2)
+    F, lam = plan.factors()
+    size = plan.lib.cpd_workspace_size(ctypes.byref(plan.desc))
+    plan.close()
+    return fits, F + [lam], size
+
+
+@pytest.mark.parametrize("n,r_thc,r_cp", [(100, 500, 400), (45, 523, 170)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_tile_forms_and_tuner_keep_the_bits(n, r_thc, r_cp, precision):
+    """A plan in each tile form, a tuned plan and the plan that follows it
+    (which takes the tuned forms from the start): the same fits, factors and
+    workspace size."""
+    from paper_2502_17683_amd import test_tile_force
+    say(f"forms n={n} r_thc={r_thc} r_cp={r_cp} {precision}")
+    X, Z = make_thc(n, r_thc, 5)
+    X, Z = to_dev(X), to_dev(Z)
+    init = [to_dev(f) for f in init_factors([n] * 4, r_cp, 1000)]
+    got = []
+    try:
+        for bm in (32, 64, 128):
+            test_tile_force(bm)
+            got.append(_run(X, Z, r_cp, init, precision=precision))
+    finally:
+        test_tile_force(0)
+    for tune in (False, True, True, False):
+        got.append(_run(X, Z, r_cp, init, precision=precision, autotune=tune))
+    for fits, F, size in got[1:]:
+        assert fits == got[0][0] and size == got[0][2]
+        for a, b in zip(F, got[0][1]):
+            assert torch.equal(a, b)

@@ -85,12 +85,18 @@ struct Prob {
 };
 
 // One grouped launch: device table + workgroup prefix sums.
+// One launch of a grouped product: entries first .. first + count - 1, whose
+// prefix sums start at offs + at.
+struct GemmRun {
+  int first, count, at, total;
+};
 struct GroupOp {
   void* tab = nullptr;   // device: GemmArgs<T>[] / SplitArgs[]
-  int* offs = nullptr;   // device: nprob + 1 prefix sums
-  int total = 0;
+  int* offs = nullptr;   // device: prefix sums, one more than entries (per launch)
+  int total = 0;         // split BF16: workgroups
   int count = 0;         // table entries
   int bm = 64;
+  std::vector<GemmRun> runs;  // FP64 / FP32 products (one launch, unless their partial tiles pass PART_BYTES)
   bool a_t = false, b_t = false, apair = false, bpair = false;
   bool wide = false;     // split BF16: bm x 256 tiles (gemm_split_wide_group)
   int kparts = 1;        // split BF16, wide tiles: K slices (split-K) summed by a reduce launch
@@ -367,8 +373,8 @@ struct TableBuilder {
   // products of a plan, which run one after the other on its stream
   char* part = nullptr;
   int32_t* cnt = nullptr;
-  size_t part_cap = (size_t)128 << 20, part_need = 0;
-  int cnt_cap = 1 << 16, cnt_need = 0;
+  size_t part_need = 0;
+  int cnt_need = 0;
   template <typename X>
   void* put(const std::vector<X>& v) {
     const size_t bytes = sizeof(X) * v.size();
@@ -397,43 +403,54 @@ std::vector<int> gemm_forms(const std::vector<GemmArgs<T>>& v) {
   return {32, 64, 128};
 }
 
-// Fills the split and layout fields of the entries for tile form bm and
-// returns the prefix sums of their workgroups.  The room for the partial
-// tiles is that of the form that needs most, so that the size of a workspace
-// and the split of a product follow from the shapes alone, whichever form
-// the tuner has taken or tries.
+// Fills the split and layout fields of the entries for tile form bm, cuts
+// them into launches and returns the prefix sums of the launches' workgroups
+// (one more element per launch than entries).  The room for the partial
+// tiles is that of the form that needs most, so that the size of a workspace,
+// the split of a product and the launches follow from the shapes alone,
+// whichever form the tuner has taken or tries.  A batch whose partial tiles
+// pass PART_BYTES runs in several launches that use the region in turn: no
+// product loses its split, so a problem gives the same bits alone and in any
+// batch.  (A product's own partial tiles are those of some 256 workgroups, 2
+// to 8 MB: a launch of PART_BYTES fills the chip many times over.)
+constexpr size_t PART_BYTES = (size_t)128 << 20;
 template <typename T>
-std::vector<int> gemm_entries(TableBuilder& tb, std::vector<GemmArgs<T>>& v, int bm) {
-  size_t bytes = 0;
-  int cnts = 0;
+std::vector<int> gemm_entries(TableBuilder& tb, std::vector<GemmArgs<T>>& v, int bm, std::vector<GemmRun>& runs) {
   auto need = [](const GemmArgs<T>& g, int f) {
     return g.slices > 1 ? gemm_tile_count(g.M, g.N, f, g.lower) - g.nfull : 0;
   };
   const std::vector<int> forms = gemm_forms(v);
-  for (auto& g : v) {
-    size_t room = 0;
+  std::vector<int> offs;
+  size_t room = 0, at = 0;
+  int cnts = 0, c = 0;
+  runs.clear();
+  for (int i = 0; i < (int)v.size(); ++i) {
+    GemmArgs<T>& g = v[i];
+    size_t bytes = 0;
     int most = 0;
     for (int f : forms) {
-      room = std::max(room, sizeof(T) * (size_t)need(g, f) * g.slices * f * f);
+      bytes = std::max(bytes, sizeof(T) * (size_t)need(g, f) * g.slices * f * f);
       most = std::max(most, need(g, f));
     }
-    bytes += room;
+    if (runs.empty() || room + bytes > PART_BYTES) {
+      runs.push_back({i, 0, (int)offs.size(), 0});
+      offs.push_back(0);
+      room = at = 0;
+      cnts = c = 0;
+    }
+    room += bytes;
     cnts += most;
-  }
-  const bool fits = bytes <= tb.part_cap && cnts <= tb.cnt_cap;
-  if (fits && bytes > tb.part_need) tb.part_need = bytes;
-  if (fits && cnts > tb.cnt_need) tb.cnt_need = cnts;
-  std::vector<int> offs(1, 0);
-  size_t at = 0;
-  int c = 0;
-  for (auto& g : v) {
-    if (!fits) g.slices = 1;
+    tb.part_need = std::max(tb.part_need, room);
+    tb.cnt_need = std::max(tb.cnt_need, cnts);
     const int t = need(g, bm);
     g.part = t ? tb.part + at : nullptr;
     g.cnt = t ? tb.cnt + c : nullptr;
     at += sizeof(T) * (size_t)t * g.slices * bm * bm;
     c += t;
-    offs.push_back(offs.back() + gemm_units(g, bm));
+    GemmRun& r = runs.back();
+    r.count += 1;
+    r.total += gemm_units(g, bm);
+    offs.push_back(r.total);
   }
   return offs;
 }
@@ -462,8 +479,7 @@ GroupOp gemm_op(TableBuilder& tb, std::vector<GemmArgs<T>> v, bool at, bool bt, 
     auto it = g_tune.find(tune_key(kind, dims));
     if (it != g_tune.end()) op.bm = it->second;
   }
-  const std::vector<int> offs = gemm_entries(tb, v, op.bm);
-  op.total = offs.back();
+  const std::vector<int> offs = gemm_entries(tb, v, op.bm, op.runs);
   op.tab = tb.put(v);
   op.offs = (int*)tb.put(offs);
   return op;
@@ -961,9 +977,7 @@ size_t build_tables(cpd_plan_s* p, char* base, std::vector<char>* host) {
   tb.L.base = base;
   if (base) {
     tb.part = p->ws + p->part_off;
-    tb.part_cap = p->part_bytes;
     tb.cnt = (int32_t*)(p->ws + p->cnt_off);
-    tb.cnt_cap = p->cnt_count;
   }
   if (p->prec == CPD_FP32) build_typed<float>(tb, p, &Prob::b32, false);
   else build_typed<double>(tb, p, &Prob::b64, p->prec == CPD_MIXED_BF16);
@@ -1141,7 +1155,8 @@ void split_inputs(Prob& q, hipStream_t s, std::map<const void*, int>& done_split
 template <typename T>
 void run_gemm(cpd_plan_s* p, hipStream_t s, const GroupOp& op) {
   (void)p;
-  gemm_group<T>(s, (const GemmArgs<T>*)op.tab, op.offs, op.count, op.total, op.a_t, op.b_t, op.bm);
+  for (const GemmRun& r : op.runs)
+    gemm_group<T>(s, (const GemmArgs<T>*)op.tab + r.first, op.offs + r.at, r.count, r.total, op.a_t, op.b_t, op.bm);
 }
 void run_split(cpd_plan_s* p, hipStream_t s, const GroupOp& op) {
   (void)p;
@@ -1477,11 +1492,9 @@ void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
   // prefix sums are written over the op's own
   TableBuilder tb;
   tb.part = p->ws + p->part_off;
-  tb.part_cap = p->part_bytes;
   tb.cnt = (int32_t*)(p->ws + p->cnt_off);
-  tb.cnt_cap = p->cnt_count;
   auto tune = [&](GroupOp& op, const std::string& kind) {
-    if (op.total == 0 || !op.tab) return;
+    if (op.count == 0 || !op.tab) return;
     std::vector<GemmArgs<T>> host(op.count);
     if (hipMemcpy(host.data(), op.tab, sizeof(GemmArgs<T>) * op.count, hipMemcpyDeviceToHost) != hipSuccess)
       return;
@@ -1504,14 +1517,15 @@ void autotune_ops(cpd_plan_s* p, hipStream_t s, bool gram_only = false) {
     int best_bm = op.bm;
     for (int bm : gemm_forms(host)) {
       std::vector<GemmArgs<T>> v(host);
-      const std::vector<int> offs = gemm_entries(tb, v, bm);
+      GroupOp cand = op;
+      cand.bm = bm;
+      const std::vector<int> offs = gemm_entries(tb, v, bm, cand.runs);
       if (hipMemcpy(op.tab, v.data(), sizeof(GemmArgs<T>) * v.size(), hipMemcpyHostToDevice) != hipSuccess) return;
       if (hipMemcpy(op.offs, offs.data(), sizeof(int) * offs.size(), hipMemcpyHostToDevice) != hipSuccess) return;
       float ms = 0.f;
       for (int w = 0; w < 2; ++w) {  // second pass is the timed one
         (void)hipEventRecord(e0, s);
-        for (int r = 0; r < 3; ++r)
-          gemm_group<T>(s, (const GemmArgs<T>*)op.tab, op.offs, op.count, offs.back(), op.a_t, op.b_t, bm);
+        for (int r = 0; r < 3; ++r) run_gemm<T>(p, s, cand);
         (void)hipEventRecord(e1, s);
         (void)hipEventSynchronize(e1);
         (void)hipEventElapsedTime(&ms, e0, e1);

@@ -50,3 +50,29 @@ def test_tile_forms_and_tuner_keep_the_bits(n, r_thc, r_cp, precision):
         assert fits == got[0][0] and size == got[0][2]
         for a, b in zip(F, got[0][1]):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,r_thc,r_cp,count", [(100, 500, 400, 100), (130, 650, 520, 60)])
+def test_batch_past_the_partial_tiles_of_one_launch(n, r_thc, r_cp, count):
+    """The partial tiles of all problems' back-projections pass the 128 MB
+    that one launch may take: every problem gives the bits it gives alone."""
+    from paper_2502_17683_amd import CPD, CPDBatch
+    say(f"large batch {count} x n={n} r_thc={r_thc} r_cp={r_cp}")
+    X, Z = make_thc(n, r_thc, 6)
+    X, Z = to_dev(X), to_dev(Z)
+    inits = [[to_dev(f) for f in init_factors([n] * 4, r_cp, 2000 + i)] for i in range(3)]
+    b = CPDBatch([dict(X=X, Z=Z, r_cp=r_cp, init=inits[i % 3]) for i in range(count)], precision="fp64", tol=0.0,
+                 fit_floor=0.0)
+    fb = b.sweep(1)
+    for k in range(3):
+        single = CPD(X, Z, r_cp, inits[k], tol=0.0, fit_floor=0.0)
+        fs = single.sweep(1)
+        Fs, _ = single.factors()
+        single.close()
+        for i in range(k, count, 3):
+            assert fb[i] == fs, (i, fb[i], fs)
+        for i in (k, k + count // 6 * 3, k + (count - 1 - k) // 3 * 3):
+            Fb, _ = b.factors(i)
+            for m in range(4):
+                assert torch.equal(Fs[m], Fb[m]), (i, m)
+    b.close()

@@ -1113,7 +1113,7 @@ int setup_norm2(Prob& q, hipStream_t s) {
     hadamard_inplace_f64(s, A, B, cnt);
   }
   {
-    GemmF64 g{Rt, Rt, Rt, q.d.Z, Rt, true, A, nullptr, Rt, false, C, Rt, nullptr, 1.0, 0.0, nullptr};
+    GemmF64 g{Rt, Rt, Rt, q.d.Z, Rt, true, A, nullptr, Rt, false, C, Rt, 1.0, 0.0};
     gemm_f64(s, g);
   }
   if (!(X[2] == X[0] && X[3] == X[1])) {
@@ -1125,7 +1125,7 @@ int setup_norm2(Prob& q, hipStream_t s) {
     }
   }
   {
-    GemmF64 g{Rt, Rt, Rt, q.d.Z, Rt, false, A, nullptr, Rt, false, B, Rt, nullptr, 1.0, 0.0, nullptr};
+    GemmF64 g{Rt, Rt, Rt, q.d.Z, Rt, false, A, nullptr, Rt, false, B, Rt, 1.0, 0.0};
     gemm_f64(s, g);
   }
   transposed_dot_f64(s, C, B, Rt, Rt, q.partials, q.norm2);

@@ -63,8 +63,7 @@ cpd_status cpd_df_to_thc(int32_t n, int32_t n_aux, const double* B, double* X0, 
   if (norm2) {
     // ||G||^2 = ||B^T B||_F^2; B^T B (n_aux^2 <= n^4 values) is staged in Z
     // before Z itself is formed
-    GemmF64 g{n_aux, n_aux, n * n, B, n_aux, true, B, nullptr, n_aux, false, Z, n_aux, nullptr, 1.0, 0.0,
-              nullptr};
+    GemmF64 g{n_aux, n_aux, n * n, B, n_aux, true, B, nullptr, n_aux, false, Z, n_aux, 1.0, 0.0};
     gemm_f64(s, g);
     hipLaunchKernelGGL(sum_squares_kernel, dim3(1), dim3(256), 0, s, Z, (size_t)n_aux * n_aux, norm2);
   }
@@ -74,7 +73,7 @@ cpd_status cpd_df_to_thc(int32_t n, int32_t n_aux, const double* B, double* X0, 
   hipLaunchKernelGGL(pair_selection_kernel, dim3(grid, 2), dim3(256), 0, s, n, X0, X1);
   const int nn = n * n;
   // Z = B B^T
-  GemmF64 g{nn, nn, n_aux, B, n_aux, false, B, nullptr, n_aux, true, Z, nn, nullptr, 1.0, 0.0, nullptr};
+  GemmF64 g{nn, nn, n_aux, B, n_aux, false, B, nullptr, n_aux, true, Z, nn, 1.0, 0.0};
   gemm_f64(s, g);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
 }

@@ -643,7 +643,7 @@ cpd_status cpd_lt_exchange(int32_t n_occ, int32_t n_virt, int32_t r_thc, int32_t
   // projections (A = X^T, stored n x R_thc) and the double-term overlaps
   // (A = F^T, stored n x R_cp), all against the scaled stacks
   auto proj = [&](const double* A, int lda, int M, int K, const double* B, double* C) {
-    GemmF64 g{M, L, K, A, lda, true, B, nullptr, L, false, C, L, nullptr, 1.0, 0.0, nullptr};
+    GemmF64 g{M, L, K, A, lda, true, B, nullptr, L, false, C, L, 1.0, 0.0};
     gemm_f64(s, g);
   };
   proj(X_occ, Rt, Rt, o, buf(l.fs[0]), buf(l.w[0]));   // W0 = X_occ^T F0s
@@ -655,7 +655,7 @@ cpd_status cpd_lt_exchange(int32_t n_occ, int32_t n_virt, int32_t r_thc, int32_t
     // product's k-step is twice that of the paired-operand form (about 20%
     // faster at R_thc = 1920), which outweighs one element-wise pass
     hadamard_inplace_f64(s, buf(l.w[2]), buf(l.w[3]), (size_t)Rt * L);
-    GemmF64 g{Rt, L, Rt, Z, Rt, false, buf(l.w[2]), nullptr, L, false, buf(l.y), L, nullptr, 1.0, 0.0, nullptr};
+    GemmF64 g{Rt, L, Rt, Z, Rt, false, buf(l.w[2]), nullptr, L, false, buf(l.y), L, 1.0, 0.0};
     gemm_f64(s, g);
   }
   hipLaunchKernelGGL(single_dot_kernel, dim3(l.chunks, n_points), dim3(256), 0, s, buf(l.w[0]), buf(l.w[1]),
@@ -685,8 +685,8 @@ cpd_status cpd_lt_exchange(int32_t n_occ, int32_t n_virt, int32_t r_thc, int32_t
     const double* partner[4] = {F0, F3, F2, F1};
     for (int m = 0; m < 4; ++m) {
       // C_m = Es_m^T partner_m  (L x R)
-      GemmF64 g{L, R, rows[m], buf(l.es[m]), L, true, partner[m], nullptr, R, false, buf(l.c[m]), R, nullptr,
-                1.0, 0.0, nullptr};
+      GemmF64 g{L, R, rows[m], buf(l.es[m]), L, true, partner[m], nullptr, R, false, buf(l.c[m]), R,
+                1.0, 0.0};
       gemm_f64(s, g);
     }
     hipLaunchKernelGGL(double_dot_sep_kernel, dim3(l.dchunks, n_points), dim3(256), 0, s, buf(l.c[0]),
@@ -747,7 +747,7 @@ cpd_status cpd_lt_mp2(int32_t n_occ, int32_t n_virt, int32_t r_thc, int32_t n_po
   }
   auto gemm = [&](int M, int N, int Kd, const double* A, int lda, bool at, const double* B, int ldb, bool bt,
                   double* C, int ldc) {
-    GemmF64 g{M, N, Kd, A, lda, at, B, nullptr, ldb, bt, C, ldc, nullptr, 1.0, 0.0, nullptr};
+    GemmF64 g{M, N, Kd, A, lda, at, B, nullptr, ldb, bt, C, ldc, 1.0, 0.0};
     gemm_f64(s, g);
   };
   gemm(Rt, L, o, X_occ, Rt, true, buf(l.xs[0]), L, false, buf(l.om), L);   // O = X_o^T Xs_o

@@ -11,8 +11,10 @@
 //     lane (below).  Every product of a plan takes this form.
 //   - register-staged 64 x 64 tiles, 256 threads = 2 x 2 waves, k-step 16
 //     through LDS in k-major form, the next k-tile prefetched into
-//     registers: single products of any shape and alignment, and products
-//     with a Hadamard pair operand.
+//     registers: single products of the other shapes and alignments.  It
+//     also takes a Hadamard pair operand, which cpd_test_gemm alone still
+//     passes (the pair operands of a plan are formed in the epilogue of the
+//     product before).
 #include "kernels.h"
 #include "mfma.h"
 
@@ -29,30 +31,13 @@ __device__ __forceinline__ void gemm_body(const GemmArgs<T>& p, int bid_in, int 
   __shared__ T As[BK][BM + PAD];
   __shared__ T Bs[BK][BN + PAD];
 
-  if (p.done && *p.done) return;
-  if (p.gate && *p.gate != p.want) return;
-  const int tiles_n = (p.N + BN - 1) / BN;
-  const int bid = xcd_remap(bid_in, nblocks);
-  int m0, n0;
-  if (BM == BN && p.lower && p.M == p.N) {
-    // only the lower tiles are launched, in row order (row r holds r + 1);
-    // the XCD remap above then spreads them evenly
-    int r = (int)((sqrtf(8.f * (float)bid + 1.f) - 1.f) * 0.5f);
-    while ((r + 1) * (r + 2) / 2 <= bid) ++r;
-    while (r * (r + 1) / 2 > bid) --r;
-    m0 = r * BM;
-    n0 = (bid - r * (r + 1) / 2) * BN;
-  } else {
-    int tm, tn;
-    grouped_tile(bid, (p.M + BM - 1) / BM, tiles_n, 8, tm, tn);
-    m0 = tm * BM;
-    n0 = tn * BN;
-    if (p.lower && n0 > m0 + BM - 1) return;  // tile strictly above the diagonal
-  }
+  int tm, tn;
+  grouped_tile(xcd_remap(bid_in, nblocks), (p.M + BM - 1) / BM, (p.N + BN - 1) / BN, 8, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wm = wid >> 1, wn = wid & 1;
   const gptr<const T> gA = as_global(p.A), gB1 = as_global(p.B1), gB2 = as_global(p.B2);
-  const gptr<T> gC = as_global(p.C), gC2 = as_global(p.C2);
+  const gptr<T> gC = as_global(p.C);
 
   // Operand loads are unconditional: interior tiles (the whole k-tile in
   // range) load without checks; edge tiles read offset 0 for an
@@ -179,7 +164,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs<T>& p, int bid_in, int 
           T v = p.alpha * acc[a][b][r];
           if (p.beta != T(0)) v += p.beta * gC[off];
           gC[off] = v;
-          if (p.C2) gC2[off] = v;
         }
       }
 }
@@ -253,7 +237,7 @@ typedef __attribute__((address_space(3))) void* lds_vptr;
 struct TileBig {    // 128 x 128, eight waves of 32 x 64, two workgroups per compute unit
   static constexpr int BM = 128, BN = 128, WM = 4, WN = 2, BKB = 128, ST = 2, WPE = 4;
 };
-struct TileMid {    // 64 x 64, four waves of 32 x 32, four or five workgroups per compute unit
+struct TileMid {    // 64 x 64, four waves of 32 x 32, four workgroups per compute unit (32 KB of LDS each and a flag)
   static constexpr int BM = 64, BN = 64, WM = 2, WN = 2, BKB = 128, ST = 2, WPE = 4;
 };
 struct TileSmall {  // 32 x 32, four waves of 16 x 16, long k-steps, four stages
@@ -743,7 +727,7 @@ static void launch_tile_single(hipStream_t s, const GemmArgs<T>& a, bool at, boo
 
 template <typename T>
 static void launch_staged(hipStream_t s, const GemmArgs<T>& a, bool at, bool bt, bool had) {
-  const dim3 grid(gemm_tile_count(a.M, a.N, 64, a.lower)), block(256);
+  const dim3 grid(gemm_tile_count(a.M, a.N, 64)), block(256);
 #define THCCP_GEMM_CASE(AT_, BT_, HAD_)                                                 \
   if (at == AT_ && bt == BT_ && had == HAD_) {                                          \
     hipLaunchKernelGGL((gemm_kernel<T, 64, 64, AT_, BT_, HAD_>), grid, block, 0, s, a); \
@@ -773,7 +757,7 @@ static void gemm_dispatch(hipStream_t s, GemmArgs<T> a, bool at, bool bt) {
 }
 
 void gemm_f64(hipStream_t s, const GemmF64& g) {
-  GemmArgs<double> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
+  GemmArgs<double> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, nullptr, g.alpha, g.beta, nullptr};
   gemm_dispatch<double>(s, a, g.a_t, g.b_t);
 }
 
@@ -783,8 +767,8 @@ void gemm_f64(hipStream_t s, const GemmF64& g) {
 // LDS reads eight products ahead (84 us one product ahead), beside the other
 // product (17 us alone at 8192 x 256 x 256) 78 us.
 void gemm_f32_two(hipStream_t s, const GemmF32& g, const GemmF32& h) {
-  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
-  GemmArgs<float> b{h.M, h.N, h.K, h.A, h.lda, h.B1, h.B2, h.ldb, h.C, h.ldc, h.C2, h.alpha, h.beta, h.done};
+  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, nullptr, g.alpha, g.beta, nullptr};
+  GemmArgs<float> b{h.M, h.N, h.K, h.A, h.lda, h.B1, h.B2, h.ldb, h.C, h.ldc, nullptr, h.alpha, h.beta, nullptr};
   if (!g.a_t || g.b_t || h.a_t || !h.b_t || !gemm_tile_ok(a, true, false) || !gemm_tile_ok(b, false, true)) {
     gemm_f32(s, g);
     gemm_f32(s, h);
@@ -806,7 +790,7 @@ void syrk_f64(hipStream_t s, int n, int K, const double* X, int ld, double* C, i
 }
 
 void gemm_f32(hipStream_t s, const GemmF32& g) {
-  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, g.C2, g.alpha, g.beta, g.done};
+  GemmArgs<float> a{g.M, g.N, g.K, g.A, g.lda, g.B1, g.B2, g.ldb, g.C, g.ldc, nullptr, g.alpha, g.beta, nullptr};
   gemm_dispatch<float>(s, a, g.a_t, g.b_t);
 }
 

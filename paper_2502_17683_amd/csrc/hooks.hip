@@ -135,11 +135,11 @@ cpd_status cpd_test_gemm(int32_t fp32, int32_t M, int32_t N, int32_t K, const vo
   hipStream_t s = (hipStream_t)stream;
   if (fp32) {
     GemmF32 g{M, N, K, (const float*)A, lda, a_t != 0, (const float*)B1, (const float*)B2, ldb, b_t != 0,
-              (float*)C, ldc, nullptr, 1.f, 0.f, nullptr};
+              (float*)C, ldc, 1.f, 0.f};
     gemm_f32(s, g);
   } else {
     GemmF64 g{M, N, K, (const double*)A, lda, a_t != 0, (const double*)B1, (const double*)B2, ldb,
-              b_t != 0, (double*)C, ldc, nullptr, 1.0, 0.0, nullptr};
+              b_t != 0, (double*)C, ldc, 1.0, 0.0};
     gemm_f64(s, g);
   }
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;

@@ -58,17 +58,15 @@ struct GemmF64 {
   int M, N, K;
   const double* A; int lda; bool a_t;
   const double* B1; const double* B2; int ldb; bool b_t;
-  double* C; int ldc; double* C2;
+  double* C; int ldc;
   double alpha, beta;
-  const int32_t* done;
 };
 struct GemmF32 {
   int M, N, K;
   const float* A; int lda; bool a_t;
   const float* B1; const float* B2; int ldb; bool b_t;
-  float* C; int ldc; float* C2;
+  float* C; int ldc;
   float alpha, beta;
-  const int32_t* done;
 };
 void gemm_f64(hipStream_t s, const GemmF64& g);
 void gemm_f32(hipStream_t s, const GemmF32& g);

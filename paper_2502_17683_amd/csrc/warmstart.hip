@@ -953,7 +953,7 @@ cpd_status cpd_ws_labels(const int32_t n[4], int32_t r_thc, int32_t r_cp, const 
   int* colused = c.take<int>(Rc + R);
   int* match = c.take<int>(Rc + R);
   hipStream_t st = (hipStream_t)stream;
-  GemmF64 g{r_cp, r_thc, n[0], F[0], r_cp, true, X[0], nullptr, r_thc, false, C, r_thc, nullptr, 1.0, 0.0, nullptr};
+  GemmF64 g{r_cp, r_thc, n[0], F[0], r_cp, true, X[0], nullptr, r_thc, false, C, r_thc, 1.0, 0.0};
   gemm_f64(st, g);
   hipLaunchKernelGGL(col_norms_kernel, dim3((r_cp + 255) / 256), dim3(256), 0, st, F[0], n[0], r_cp, fn);
   hipLaunchKernelGGL(col_norms_kernel, dim3((r_thc + 255) / 256), dim3(256), 0, st, X[0], n[0], r_thc, xn);
@@ -983,8 +983,8 @@ cpd_status cpd_mlp_forward(const float* params, const float* x, const int32_t* i
   hipStream_t s = (hipStream_t)stream;
   MlpWs w = carve_mlp(workspace, rows);
   hipLaunchKernelGGL(l1_fwd_kernel, dim3((rows + L1R - 1) / L1R), dim3(256), 0, s, params, x, idx, rows, w.h1);
-  GemmF32 g{rows, WIDTH, WIDTH, w.h1, WIDTH, false, params + OFF_W2, nullptr, WIDTH, false, w.z2, WIDTH, nullptr,
-            1.f, 0.f, nullptr};
+  GemmF32 g{rows, WIDTH, WIDTH, w.h1, WIDTH, false, params + OFF_W2, nullptr, WIDTH, false, w.z2, WIDTH,
+            1.f, 0.f};
   gemm_f32(s, g);
   hipLaunchKernelGGL(l3_fwd_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, params, w.z2, rows, out);
   return hipGetLastError() == hipSuccess ? CPD_OK : CPD_ERR_HIP;
@@ -1013,10 +1013,10 @@ cpd_status cpd_mlp_backward(const float* params, const float* x, const int32_t* 
   const dim3 chunks((rows + CHUNK - 1) / CHUNK, WIDTH / CG);
   hipLaunchKernelGGL(bwd3_kernel, chunks, dim3(256), 0, s, params, dout, w.z2, rows, w.d2, w.part);
   // layer 2: dW2 = h1^T da2, dh1 = da2 W2^T
-  GemmF32 gw{WIDTH, WIDTH, rows, w.h1, WIDTH, true, w.d2, nullptr, WIDTH, false, grads + OFF_W2, WIDTH, nullptr,
-             1.f, 0.f, nullptr};
-  GemmF32 gd{rows, WIDTH, WIDTH, w.d2, WIDTH, false, params + OFF_W2, nullptr, WIDTH, true, w.d1, WIDTH, nullptr,
-             1.f, 0.f, nullptr};
+  GemmF32 gw{WIDTH, WIDTH, rows, w.h1, WIDTH, true, w.d2, nullptr, WIDTH, false, grads + OFF_W2, WIDTH,
+             1.f, 0.f};
+  GemmF32 gd{rows, WIDTH, WIDTH, w.d2, WIDTH, false, params + OFF_W2, nullptr, WIDTH, true, w.d1, WIDTH,
+             1.f, 0.f};
   gemm_f32_two(s, gw, gd);
   hipLaunchKernelGGL(bwd1_kernel, chunks, dim3(256), 0, s, params, w.d1, x, idx, rows, w.part);
   hipLaunchKernelGGL(grad_sum_kernel, dim3((PG_LEN + 63) / 64), dim3(64), 0, s, w.part, (int)chunks.x, grads);

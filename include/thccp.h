@@ -21,7 +21,11 @@
  *   - All matrices are row-major, densely packed (leading dimension = number
  *     of columns), float64, in DEVICE memory unless stated otherwise.
  *   - Pointers passed in are borrowed: the library never frees them and
- *     they must stay valid for the life of the plan.
+ *     they must stay valid, and the values of X and Z the same, for the life
+ *     of the plan.  (An FP64 or split-BF16 plan reads X and Z in place where
+ *     r_thc is even and they are 16-byte aligned; otherwise, and in FP32, it
+ *     copies them into its workspace at init.  So the workspace size follows
+ *     from a descriptor with the plan's own X and Z.)
  *   - The library allocates no device memory: all state lives in the
  *     caller's workspace (size from cpd_workspace_size).  It creates one
  *     private HIP stream per plan for graph capture.

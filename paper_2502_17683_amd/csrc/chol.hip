@@ -541,7 +541,7 @@ __device__ __forceinline__ bool strip_potrf4_panel(T d[16], T e[16], T* invd, T*
 // cycles each; they share the unit with the matrix instructions, so nothing
 // hides them): 20.7k cycles a block, 11.6k of them in the four panels'
 // columns, against 23.0k of the strip form; the diagonal workgroup, whose
-// X_k = L_kk^{-double} rides along, saves its separate substitution besides.
+// X_k = L_kk^{-T} rides along, saves its separate substitution besides.
 // N = 100, R_cp = 400, four sweeps: 3.13 -> 2.80 ms; (41, 203), R_cp = 491,
 // two sweeps: 1.96 -> 1.78 ms; N = 20: 967 -> 855 us.
 __device__ double dpp_f64(double old, double v, int ctrl, int row_mask, int bank_mask, bool bound)
@@ -717,8 +717,10 @@ __device__ __forceinline__ void load_acc(typename Acc4<T>::type acc[4], const T*
 }
 // V_ik of the dataflow factorisation, from V or as the Hadamard product of
 // the Grams with the identity on the padding: bitwise what form_v_group
-// writes, without its launch and its pass over V (4 us of a mode update at
-// N = 20, 54 us at R_cp = 4000).  N = 20, four sweeps: 860 -> 803 us; N =
+// writes, without its launch and its pass over V.  (Of a diagonal block only
+// the lower triangle is valid, and only that is used: Grams in 32-tiles
+// leave out the block's upper quadrant.)  The launch and the pass took 4 us
+// of a mode update at N = 20, 54 us at R_cp = 4000.  N = 20, four sweeps: 860 -> 803 us; N =
 // 100: 2.80 -> 2.76 ms; N = 800, one sweep: 18.01 -> 17.86 ms.
 template <typename T>
 __device__ __forceinline__ void load_v(typename Acc4<T>::type acc[4], const StepProb<T>& q, int i, int k, int Tp,

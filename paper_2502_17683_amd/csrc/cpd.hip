@@ -1019,18 +1019,26 @@ size_t layout_plan(cpd_plan_s* p, char* base) {
 // own shape and precision:
 //   - up to INV_BLOCKS block columns.  The identity's rows are nblk^2 / 2
 //     more tiles of the forward solve, free while they find idle units.  A
-//     sweep of one problem alone, inverse form against block pairs: R_cp =
-//     256 517 : 615 us, 400 772 : 937, 640 1068 : 1258, 1000 1705 : 1966; a
-//     batch that fills the chip: 32 x R_cp 400 2063 : 2114, 16 x 640 2427 :
-//     2423, 16 x 768 3209 : 3125, 16 x 960 4786 : 4449.  (The choice may not
-//     look at the batch: a problem gives the same bits alone and in any.
-//     Both sides with the strip form of the diagonal blocks.)
+//     sweep of one problem alone, inverse form against block pairs (both
+//     with the panel form of the diagonal blocks; n = R_cp / 4, R_thc = 5
+//     n): R_cp = 60 180 : 192 us, 128 259 : 313, 256 415 : 514, 400 667 :
+//     828, 640 946 : 1141, 768 1228 : 1451, 1000 1607 : 1876.  Batches that
+//     fill the chip: 64 x R_cp 128 453 : 514, 64 x 256 1193 : 1269, 32 x 400
+//     1829 : 1872, 48 x 400 2529 : 2508, 16 x 512 1595 : 1678, 16 x 640 2489
+//     : 2529, and past the limit 16 x 768 3775 : 3640, 16 x 960 6156 : 5759.
+//     (The choice may not look at the batch: a problem gives the same bits
+//     alone and in any.)
 //   - FP64 plans only.  FP32 and split-BF16 plans keep the rounding of the
 //     substitution: their low-precision products carry a last bit on (a
 //     sweep of the Laplace batch moved by 9e-5).
-// The solution's error is that of the substitution (collinear factors, R_cp
-// 100 .. 500, cond(V) 3e4 .. 6e6: 1.7e-12 .. 2.5e-10 either way); the
-// residual is not as small (4e-16 against 6e-16 .. 2e-13).
+// The error of the solution is that of the block pairs: factors and weights
+// of a sweep against 80-bit arithmetic, 44 problems of R_cp 34 .. 640, 0.99
+// times theirs in the geometric mean, and 24 with nearly collinear initial
+// factors (cond(V) up to 4e5) 1.01 times.  The residual |F V - M| / (|F|
+// |V|) is not as small where V is ill-conditioned and wide: 1.3e-16 ..
+// 1.9e-16 against 1.0e-16 .. 1.7e-16 up to cond(V) = 200 and R_cp = 400,
+// but at R_cp = 640 4.3e-16 against 1.2e-16 (cond 2e3) and 3.9e-15 against
+// 1.6e-15 (2e5).
 constexpr int INV_BLOCKS = 10;
 bool inverse_form(const Prob& q, int prec, int panel) {
   return prec == CPD_FP64 && panel <= 0 && get_bwd_form() == 0 && q.nblk <= INV_BLOCKS;

@@ -651,9 +651,8 @@ cpd_status cpd_lt_exchange(int32_t n_occ, int32_t n_virt, int32_t r_thc, int32_t
   proj(X_occ, Rt, Rt, o, buf(l.fs[2]), buf(l.w[2]));   // W2 = X_occ^T F2s
   proj(X_virt, Rt, Rt, v, buf(l.fs[1]), buf(l.w[3]));  // W3 = X_virt^T F1s
   {
-    // Y = Z (W2 o W3), the Hadamard product formed in place first: the plain
-    // product's k-step is twice that of the paired-operand form (about 20%
-    // faster at R_thc = 1920), which outweighs one element-wise pass
+    // Y = Z (W2 o W3), the Hadamard product formed in place first: the
+    // direct-load tiles take no pair operand
     hadamard_inplace_f64(s, buf(l.w[2]), buf(l.w[3]), (size_t)Rt * L);
     GemmF64 g{Rt, L, Rt, Z, Rt, false, buf(l.w[2]), nullptr, L, false, buf(l.y), L, 1.0, 0.0};
     gemm_f64(s, g);

@@ -11,9 +11,10 @@ namespace thccp {
 
 // V = g0 o g1 o g2 on the R x R block, identity on the padding, plus mu I
 // on the retry pass.  blockIdx.y selects the problem.  V is symmetric and
-// the factorisation reads only its lower 64 x 64 blocks (diagonal blocks
-// whole), so only those are formed; the Grams are computed on the lower
-// tiles only, which cover them.  One workgroup per lower block (row-major
+// only its lower 64 x 64 blocks are formed, from the Grams' lower tiles.
+// Of a diagonal block only the lower triangle is valid, and the
+// factorisation uses only that: the Grams' tiles may be 32 x 32, and then
+// the block's upper right quadrant is not computed.  One workgroup per lower block (row-major
 // order: block row r holds r + 1 blocks), two adjacent elements per thread
 // and step.
 // The launch's last workgroup of a problem clears its ready flags.  (Sweeps

@@ -435,7 +435,7 @@ __global__ void zero_f32(float* a, size_t n) {
 }
 
 // ------------------------------------------------------------ network, FP32
-// The training step runs in eleven launches.  What bounded the first form of
+// The training step runs in ten launches (with the Adam update).  What bounded the first form of
 // it were its reductions over the rows: one workgroup per 256 rows and one
 // load at a time (192 us each at 8192 rows, three of them).  Now a row's
 // values are formed by many threads into LDS, and one thread per output

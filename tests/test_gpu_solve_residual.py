@@ -2,6 +2,7 @@
 condition of the normal matrix."""
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import need_gpu, say, to_dev
 from synth import init_factors, make_thc
@@ -45,3 +46,21 @@ def test_solve_residual_of_a_sweep(r_cp, precision):
     # (four values swapped in one tile, or one Gram left out of it: 4.5e-3 and more at two to four block columns)
     assert bound <= 3e-3 * np.linalg.norm(M)
     assert np.linalg.norm(S @ V - M) <= bound
+
+
+@pytest.mark.parametrize("R", [64, 100, 193])
+@pytest.mark.parametrize("panel", [0, 1])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_solve_reads_the_lower_triangle(R, panel, fp32):
+    """Grams in 32-tiles leave the upper right quadrant of a diagonal block
+    as it was: other values above the diagonal change nothing."""
+    from paper_2502_17683_amd import test_solve
+    say(f"lower triangle R={R} panel={panel} fp32={fp32}")
+    rng = np.random.default_rng(R)
+    dt = torch.float32 if fp32 else torch.float64
+    A = rng.standard_normal((R, R + 5))
+    V = A @ A.T / R + 0.5 * np.eye(R)
+    M = to_dev(rng.standard_normal((37, R)), dt)
+    F, failed = test_solve(to_dev(V, dt), M, panel=panel)
+    G, other = test_solve(to_dev(np.tril(V) + np.triu(rng.standard_normal((R, R)), 1), dt), M, panel=panel)
+    assert not failed and not other and torch.equal(F, G)

@@ -1970,12 +1970,14 @@ cpd_status cpd_kernel_times(cpd_plan p, int32_t reps, double* ms_out) {
         // normal-equation solve of mode 0: V, factorisation fused with the
         // forward solve, backward solve, normalisation
         if (f32) {
-          if (which == 5 || (which == 4 && !forms_v)) form_v_group<float>(s, (const FormVArgs<float>*)p->formv[0], p->count, p->maxTp, 0);
+          if (which == 5 || (which == 4 && !forms_v))
+            form_v_group<float>(s, (const FormVArgs<float>*)p->formv[0], p->count, p->maxTp, 0);
           if (which != 6) run_sched<float>(p, s, 0, p->steps[0].cholfwd, 0);
           if (which != 5) run_bwd<float>(p, 0, s, false, which == 6);
           if (which == 4) normalise_group<float>(s, (const NormArgs<float>*)p->norm[0], p->count, p->maxR, 0);
         } else {
-          if (which == 5 || (which == 4 && !forms_v)) form_v_group<double>(s, (const FormVArgs<double>*)p->formv[0], p->count, p->maxTp, 0);
+          if (which == 5 || (which == 4 && !forms_v))
+            form_v_group<double>(s, (const FormVArgs<double>*)p->formv[0], p->count, p->maxTp, 0);
           if (which != 6) run_sched<double>(p, s, 0, p->steps[0].cholfwd, 0);
           if (which != 5) run_bwd<double>(p, 0, s, false, which == 6);
           if (which == 4) normalise_group<double>(s, (const NormArgs<double>*)p->norm[0], p->count, p->maxR, 0);
